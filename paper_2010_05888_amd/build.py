@@ -19,7 +19,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgarfield.so")
 
-SOURCES = ["dist.hip", "select.hip", "aggregate.hip", "byzantine.hip", "segtable.hip",
+SOURCES = ["dist.hip", "ring_direct.hip", "select.hip", "aggregate.hip", "byzantine.hip", "segtable.hip",
            "contract.hip", "garfield_api.cpp", "timing.cpp"]
 
 ARCH = "gfx950"

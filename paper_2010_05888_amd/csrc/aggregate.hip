@@ -45,87 +45,16 @@ __global__ __launch_bounds__(kBlock) void k_mean_rows(const float* __restrict__ 
 }
 
 // Mean of the k distinct rows of sel from the distance step's column sums
-// (enqueue_mean_complement): thread 0 lists the rows not in sel, ascending, in
-// LDS; every lane subtracts them from its coordinates' column sums where all
-// W of those are exact (not NaN), and otherwise sums the rows of sel as
-// k_mean_rows does. Either way the fp64 value is the exact sum k_mean_rows
-// forms (sums of these values are exact where the column sum is), rounded
-// once.
+// (complement_at).
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_mean_complement(const float* __restrict__ x, int n,
                                                             int64_t d,
                                                             const int32_t* __restrict__ sel, int k,
                                                             const double* __restrict__ colsum,
                                                             float* __restrict__ out) {
-  __shared__ int32_t rest[kNmax];
-  __shared__ int nrest;
-  if (threadIdx.x == 0) {
-    uint64_t mask = 0;
-    for (int t = 0; t < k; ++t) mask |= uint64_t{1} << row_of(sel, t, n);
-    int q = 0;
-    for (int r = 0; r < n; ++r)
-      if (!((mask >> r) & 1)) rest[q++] = r;
-    nrest = q;
-  }
-  __syncthreads();
-  const int q = nrest;
-  const MatrixRows src{x, d};
-  const double count = static_cast<double>(k);
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock * W;
-  for (int64_t c = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * W; c < d;
-       c += stride) {
-    const bool full = c + W <= d;
-    double acc[W];
-    bool loaded = false;
-    if constexpr (W >= 2) {
-      if (full) {  // ordinary 16-byte loads: a line's halves meet in L2
-#pragma unroll
-        for (int e = 0; e < W; e += 2) {
-          const d2 t = *reinterpret_cast<const d2*>(colsum + c + e);
-          acc[e] = t.x;
-          acc[e + 1] = t.y;
-        }
-        loaded = true;
-      }
-    }
-    if (!loaded) {
-#pragma unroll
-      for (int e = 0; e < W; ++e) acc[e] = (c + e < d) ? colsum[c + e] : 0.0;
-    }
-    bool exact = true;
-#pragma unroll
-    for (int e = 0; e < W; ++e) exact = exact && !__builtin_isnan(acc[e]);
-    if (exact) {
-      for (int t = 0; t < q; t += 2) {  // two rows' loads in flight
-        const bool two = t + 1 < q;
-        float v[2][W];
-        const float* p0 = src.row(rest[t]) + c;
-        const float* p1 = src.row(rest[two ? t + 1 : t]) + c;
-        if (full) {
-          load_w<W>(p0, v[0]);
-          load_w<W>(p1, v[1]);
-        } else {
-          load_w_tail<W>(p0, d - c, v[0]);
-          load_w_tail<W>(p1, d - c, v[1]);
-        }
-#pragma unroll
-        for (int e = 0; e < W; ++e) acc[e] -= static_cast<double>(v[0][e]);
-        if (two) {
-#pragma unroll
-          for (int e = 0; e < W; ++e) acc[e] -= static_cast<double>(v[1][e]);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < W; ++e) acc[e] = 0.0;
-      if (full) sum_rows_at<W, true, true>(src, d, ListedRows{sel, n}, k, c, acc);
-      else sum_rows_at<W, false, true>(src, d, ListedRows{sel, n}, k, c, acc);
-    }
-    float o[W];
-#pragma unroll
-    for (int e = 0; e < W; ++e) o[e] = static_cast<float>(acc[e] / count);
-    store_out<W>(out, c, d, full, o);
-  }
+  const uint64_t chosen = rows_mask(sel, k, n);
+  const int64_t c = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * W;
+  if (c < d) complement_at<W>(MatrixRows{x, d}, n, d, sel, k, chosen, colsum, c, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -241,7 +170,7 @@ size_t static_lds_of(K kernel) {
 // and the gathers have no loop to hoist their per-row address arithmetic out
 // of (where it would hold one register pair per row). 2^31 - 1 workgroups of
 // kBlock lanes cover any d a device holds; beyond them grid_for returns 0 and
-// the launch is refused (mean_complement alone still loops).
+// the launch is refused.
 int grid_for(int64_t items) {
   const int64_t blocks = (items + kBlock - 1) / kBlock;
   if (blocks > 0x7fffffff) return 0;

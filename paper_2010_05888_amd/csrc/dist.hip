@@ -6,7 +6,7 @@
 // Every workgroup of the distance kernel is a tile: the direct engine cuts the
 // coordinates into tiles of `chunk` consecutive coordinates, the Gram engine
 // gives each workgroup the 256-coordinate stages s, s + G, s + 2G, ... of its
-// slot s (gram_slot: a permutation of the workgroups by XCD). Each tile
+// slot s (xcd_slot: a permutation of the workgroups by XCD). Each tile
 // writes one fp64 partial sum per entry (entry-major: partial[entry * tiles +
 // tile]); k_sum_tiles then adds the tiles of each entry in a fixed order, so D
 // is deterministic and depends only on (n, d), never on scheduling. The
@@ -29,6 +29,7 @@
 #include "direct_body.h"
 #include "dist_layout.h"
 #include "internal.h"
+#include "ring.h"
 #include "timing.h"
 
 namespace garfield {
@@ -69,6 +70,7 @@ __global__ __launch_bounds__(kBlock) void k_dist_direct_sum(const float* __restr
   block_reduce_pairs<P>(acc, partial + blockIdx.x, gridDim.x);
 }
 
+// ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // Gram engine, step 1: probe. The sample is kProbeRuns runs of kBlock
 // consecutive coordinates spread evenly over d (all of d in one run when d is
@@ -244,16 +246,6 @@ __host__ __device__ constexpr int pair_b2(int nb, int q) {
     ++b1;
   }
   return b1 + q;
-}
-
-// LDS-only barrier: waits for this wave's LDS operations, then for every
-// wave, and leaves vector-memory loads in flight (a __syncthreads() would also
-// wait for those).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt and expcnt unconstrained
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
 }
 
 // One 16-byte load of row `row` at coordinate c (lane l of the wave reads
@@ -666,24 +658,11 @@ __device__ __forceinline__ void gram_run(uint8_t* __restrict__ lds, int64_t cnt,
   }
 }
 
-// The workgroup's slot among the G of a launch: list entry slot + i * G is
-// its i-th stage. Workgroups are dealt to the 8 XCDs round-robin (block b to
-// XCD b % 8), so slot (b % 8) * (G / 8) + b / 8 gives each XCD a contiguous
-// run of slots, and stages next to each other, which share the cache lines
-// at the ends of their 1 KB row runs, meet in one XCD's L2 at about the same
-// time instead of being fetched by two XCDs. (A bijection on [0, G) when 8
-// divides G; other grids keep b.)
-__device__ __forceinline__ int64_t gram_slot() {
-  const int64_t b = blockIdx.x, G = gridDim.x;
-  if (G % 8 != 0) return b;
-  return (b % 8) * (G / 8) + b / 8;
-}
-
 // Entries of this workgroup's slot b among `total` list entries of which the
 // first `nfull` are full stages: (count, full count).
 __device__ __forceinline__ void gram_share(int64_t total, int64_t nfull, int64_t* cnt,
                                            int64_t* nf) {
-  const int64_t b = gram_slot(), G = gridDim.x;
+  const int64_t b = xcd_slot(), G = gridDim.x;
   *cnt = total > b ? (total - b + G - 1) / G : 0;
   *nf = nfull > b ? (nfull - b + G - 1) / G : 0;
 }
@@ -695,7 +674,7 @@ struct MatrixStages {
   int64_t d;
   int64_t nfull;
   __device__ __forceinline__ StageRef<MatrixRows> entry(int64_t i) const {
-    const int64_t li = gram_slot() + i * gridDim.x;  // list index (the partial stage is last)
+    const int64_t li = xcd_slot() + i * gridDim.x;  // list index (the partial stage is last)
     return StageRef<MatrixRows>{MatrixRows{x, d}, li * kGramStage, d, li < nfull};
   }
 };
@@ -742,7 +721,7 @@ struct TableStages {
   const GramSegs* segs;
   __device__ __forceinline__ StageRef<TableRows> entry(int64_t i) const {
     const GramSegs& t = *segs;
-    const int64_t li = gram_slot() + i * gridDim.x;
+    const int64_t li = xcd_slot() + i * gridDim.x;
     const int64_t nfull = t.ffirst[t.count];
     if (li < nfull) {
       const int sg = last_le(t.ffirst, t.count, li);
@@ -1074,17 +1053,23 @@ int64_t direct_chunk(int64_t d, int width) {
   return chunk < pass ? pass : (chunk > most ? most : chunk);
 }
 
-DistPlan plan_distances(int n, int64_t d, const float* x) {
+DistPlan plan_distances(int n, int64_t d, const float* x, DirectForm form) {
   DistPlan p;
   p.n = n;
   p.d = d;
   if (n < 2 || d == 0) return p;  // D is all zeros
   if (n <= direct_max_n()) {
     p.engine = kEngineDirect;
+    p.entries = n * (n - 1) / 2;
     p.width = load_width(x);
+    if (p.width == 4 && (form == kFormRing || (form == kFormAuto && ring_pays(n, d)))) {
+      p.ring = true;
+      p.chunk = ring_stage(n);
+      p.tiles = device_cus();
+      return p;
+    }
     if (p.width > direct_width_cap(n)) p.width = direct_width_cap(n);
     p.chunk = direct_chunk(d, p.width);
-    p.entries = n * (n - 1) / 2;
   } else {
     p.engine = kEngineGram;
     p.width = 4;  // 16-byte loads of 1 KB row runs
@@ -1157,11 +1142,15 @@ bool foldable(const DistPlan& p, int max_entries) {
 }
 
 hipError_t enqueue_distances(const float* x, const DistPlan& p, const DistWorkspace& ws,
-                             hipStream_t s, bool sum_tiles, double* colsum) {
+                             hipStream_t s, bool sum_tiles, double* colsum, const RingMean* mean) {
   hipError_t e = hipSuccess;
   if (colsum && (p.engine != kEngineDirect || p.n > kColSumMaxN)) return hipErrorInvalidValue;
   if (p.engine == kEngineNone) return hipSuccess;  // D is all zeros: nothing to compute
-  if (p.engine == kEngineDirect) {
+  if (mean && (!p.ring || p.n > kGuessMaxN)) return hipErrorInvalidValue;
+  if (p.ring) {
+    if (colsum) return hipErrorInvalidValue;
+    e = enqueue_distances_ring(x, p, ws.partial, mean, s);
+  } else if (p.engine == kEngineDirect) {
     e = launch_direct_dispatch<2>(p.n, x, p, ws.partial, colsum, s);
   } else {
     if ((e = enqueue_reference(x, p, ws, s)) != hipSuccess) return e;

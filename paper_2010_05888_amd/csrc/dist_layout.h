@@ -28,7 +28,7 @@ struct DistSums {
   int64_t tiles = 0;
 };
 
-__device__ __forceinline__ int direct_entry(int n, int i, int j) {  // i < j
+__host__ __device__ __forceinline__ constexpr int direct_entry(int n, int i, int j) {  // i < j
   return i * (2 * n - i - 1) / 2 + (j - i - 1);
 }
 

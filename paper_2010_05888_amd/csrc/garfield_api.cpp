@@ -90,52 +90,102 @@ garfield_status check_common(const float* x, int n, int f, int64_t d) {
 // selection kernel adds the tiles in the same order).
 constexpr int kFoldSelect = 4 * 16;  // k_krum_select, k_bulyan_select, k_mda_cover: 16 waves
 constexpr int kFoldMda = 4 * 4;      // k_mda_search: 4 waves
-// colsum: the scratch begins with d doubles that receive the column sums
-// (enqueue_distances' colsum).
+
 // The steps of run_distances on scratch the caller provides (`base`, at least
-// dist_workspace_bytes(plan) + align256(extra) bytes).
-garfield_status run_distances_on(const DistPlan& plan, void* base, const float* x, size_t extra,
-                                 DistSums* ds, void** extra_ptr, hipStream_t s,
-                                 int fold_entries, bool colsum);
-
-garfield_status run_distances(const float* x, int n, int64_t d, size_t extra, DistSums* ds,
-                              void** extra_ptr, hipStream_t s, int fold_entries = 0,
-                              bool colsum = false) {
-  const DistPlan plan = plan_distances(n, d, x);
-  const size_t dist_bytes = dist_workspace_bytes(plan);
-  void* base = nullptr;
-  garfield_status st = workspace(dist_bytes + align256(extra), &base);
-  if (st != GARFIELD_OK) return st;
-  return run_distances_on(plan, base, x, extra, ds, extra_ptr, s, fold_entries, colsum);
-}
-
-garfield_status run_distances_on(const DistPlan& plan, void* base, const float* x, size_t extra,
-                                 DistSums* ds, void** extra_ptr, hipStream_t s,
-                                 int fold_entries, bool colsum) {
-  (void)extra;
-  const size_t dist_bytes = dist_workspace_bytes(plan);
+// dist_workspace_bytes(plan)).
+garfield_status run_distances_on(const DistPlan& plan, void* base, const float* x, DistSums* ds,
+                                 hipStream_t s, int fold_entries, double* colsum = nullptr,
+                                 const RingMean* mean = nullptr) {
   const DistWorkspace ws = carve_dist_workspace(plan, base);
   *ds = dist_sums(plan, ws);
-  if (extra_ptr) *extra_ptr = static_cast<char*>(base) + dist_bytes;
   const bool fold = fold_entries > 0 && foldable(plan, fold_entries);
   if (fold) {
     ds->partial = ws.partial;
     ds->tiles = plan.tiles;
   }
-  double* cs = colsum ? static_cast<double*>(*extra_ptr) : nullptr;
-  return to_status(enqueue_distances(x, plan, ws, s, !fold, cs));
+  return to_status(enqueue_distances(x, plan, ws, s, !fold, colsum, mean));
+}
+
+garfield_status run_distances(const float* x, int n, int64_t d, size_t extra, DistSums* ds,
+                              void** extra_ptr, hipStream_t s, int fold_entries = 0) {
+  const DistPlan plan = plan_distances(n, d, x);
+  const size_t dist_bytes = dist_workspace_bytes(plan);
+  void* base = nullptr;
+  garfield_status st = workspace(dist_bytes + align256(extra), &base);
+  if (st != GARFIELD_OK) return st;
+  if (extra_ptr) *extra_ptr = static_cast<char*>(base) + dist_bytes;
+  return run_distances_on(plan, base, x, ds, s, fold_entries);
 }
 
 // The mean of m of the n rows reads m rows. With the column sums of the
 // distance step (d doubles written there, read here) it reads those and the
 // n - m other rows instead: fewer bytes when 2m > n + 4. Direct engine with
 // n <= kColSumMaxN only.
-bool use_colsum(const float* x, int n, int64_t d, int m) {
-  if (d == 0 || n > kColSumMaxN || 2 * m <= n + 4) return false;
-  return plan_distances(n, d, x).engine == kEngineDirect;
+bool use_colsum(const DistPlan& plan, int m) {
+  return plan.d > 0 && plan.n <= kColSumMaxN && 2 * m > plan.n + 4 &&
+         plan.engine == kEngineDirect;
 }
-size_t colsum_bytes(bool cs, int64_t d) {
-  return cs ? static_cast<size_t>(d) * sizeof(double) : 0;
+
+// How a rule that averages a selection of m rows runs, and the scratch it
+// needs after the distance step's: the guesses and the column sums, as far as
+// the call uses them.
+struct MeanPlan {
+  DistPlan dist;
+  bool guess = false, colsum = false;
+  size_t guess_bytes = 0, colsum_bytes = 0;
+  size_t bytes() const { return dist_workspace_bytes(dist) + guess_bytes + colsum_bytes; }
+};
+
+// guessable: whether the rule's selection is Multi-Krum's where it is clear
+// (the iterated rounds' is not: their last ones score no neighbour and take
+// the lowest index left).
+MeanPlan plan_mean(const float* x, int n, int f, int64_t d, int m, const float* out,
+                   bool guessable) {
+  MeanPlan p;
+  // an out inside x is written only once x has been read for good
+  const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), o0 = reinterpret_cast<uintptr_t>(out);
+  const uintptr_t row = static_cast<uintptr_t>(d) * sizeof(float);
+  const bool apart = o0 + row <= x0 || o0 >= x0 + static_cast<uintptr_t>(n) * row;
+  const bool want = guessable && apart && guess_pays(n, d, f, m, out);
+  p.dist = plan_distances(n, d, x, want ? kFormRing : kFormAuto);
+  p.guess = want && p.dist.ring;
+  p.colsum = out && use_colsum(p.dist, m);
+  // reserved whether or not the rule is guessable: the rules' sizes agree
+  p.guess_bytes = guess_pays(n, d, f, m, out) ? align256(kGuessRuns * sizeof(uint64_t)) : 0;
+  p.colsum_bytes = p.colsum ? align256(static_cast<size_t>(d) * sizeof(double)) : 0;
+  return p;
+}
+
+// A rule that averages the m rows its selection picks: distances, then
+// select(ds, scratch of `extra` bytes) into sel, then the mean into out (none
+// if null). guessable: as plan_mean's; fold: what `select` can fold.
+template <class Select>
+garfield_status select_and_mean(const float* x, int n, int f, int64_t d, int m, bool guessable,
+                                size_t extra, int fold, const int32_t* sel, float* out,
+                                hipStream_t s, Select&& select) {
+  const MeanPlan p = plan_mean(x, n, f, d, m, out, guessable);
+  void* base = nullptr;
+  garfield_status st = workspace(p.bytes() + align256(extra), &base);
+  if (st != GARFIELD_OK) return st;
+  char* at = static_cast<char*>(base) + dist_workspace_bytes(p.dist);
+  uint64_t* guess = reinterpret_cast<uint64_t*>(at);
+  at += p.guess_bytes;
+  double* colsum = p.colsum ? reinterpret_cast<double*>(at) : nullptr;
+  at += p.colsum_bytes;
+  hipError_t e = hipSuccess;
+  if (p.guess && (e = enqueue_guess(x, n, d, f, m, guess, s)) != hipSuccess) return to_status(e);
+  // the ring form writes column sums as it writes a guessed mean
+  const RingMean mean{p.guess ? guess : nullptr, colsum, out, m};
+  const bool beside = p.guess || (p.dist.ring && colsum);
+  DistSums ds;
+  st = run_distances_on(p.dist, base, x, &ds, s, fold, beside ? nullptr : colsum,
+                        beside ? &mean : nullptr);
+  if (st != GARFIELD_OK) return st;
+  st = to_status(select(ds, at));
+  if (st != GARFIELD_OK || !out) return st;
+  if (p.guess) return to_status(enqueue_mean_after(x, n, d, sel, mean, s));
+  return to_status(colsum ? enqueue_mean_complement(x, n, d, sel, m, colsum, out, s)
+                          : enqueue_mean_rows(x, n, d, sel, m, out, s));
 }
 
 // Requirements of `rule` (Section 3.1) and the number of indices it selects
@@ -242,15 +292,8 @@ garfield_status garfield_multikrum(const float* x, int n, int f, int64_t d, int 
     if (st != GARFIELD_OK) return st;
     return to_status(enqueue_krum_select_mean(x, ds, d, f, m, sel, out, s));
   }
-  const bool cs = out && use_colsum(x, n, d, m);
-  void* colsum = nullptr;
-  st = run_distances(x, n, d, colsum_bytes(cs, d), &ds, &colsum, s, kFoldSelect, cs);
-  if (st != GARFIELD_OK) return st;
-  st = to_status(enqueue_krum_select(ds, f, m, sel, s));
-  if (st != GARFIELD_OK || !out) return st;
-  if (cs)
-    return to_status(enqueue_mean_complement(x, n, d, sel, m, static_cast<double*>(colsum), out, s));
-  return to_status(enqueue_mean_rows(x, n, d, sel, m, out, s));
+  return select_and_mean(x, n, f, d, m, true, 0, kFoldSelect, sel, out, s,
+                         [&](const DistSums& dd, void*) { return enqueue_krum_select(dd, f, m, sel, s); });
 }
 
 garfield_status garfield_multikrum_noalloc(const float* x, int n, int f, int64_t d, int m,
@@ -261,8 +304,11 @@ garfield_status garfield_multikrum_noalloc(const float* x, int n, int f, int64_t
   if (n < 2 * f + 3) return GARFIELD_EREQ;
   if (m <= 0) m = n - f;
   if (m > n - f) return GARFIELD_EINVAL;
+  // What is refused follows the direct engine's register form, whose scratch
+  // grows with d; the ring form that long inputs take needs less.
+  if (dist_workspace_bytes(plan_distances(n, d, x, kFormRegisters)) > GARFIELD_NOALLOC_SCRATCH_BYTES)
+    return GARFIELD_ETOOBIG;
   const DistPlan plan = plan_distances(n, d, x);
-  if (dist_workspace_bytes(plan) > GARFIELD_NOALLOC_SCRATCH_BYTES) return GARFIELD_ETOOBIG;
   void* base = nullptr;
   st = static_scratch(&base);
   if (st != GARFIELD_OK) return st;
@@ -272,11 +318,11 @@ garfield_status garfield_multikrum_noalloc(const float* x, int n, int f, int64_t
   // (tile partials, entry sums, probe matrices, reference row), so nothing
   // needs clearing; the mean reads the selected rows (no column sums)
   if (krum_fusable(plan, out)) {
-    st = run_distances_on(plan, base, x, 0, &ds, nullptr, s, plan.entries, false);
+    st = run_distances_on(plan, base, x, &ds, s, plan.entries);
     if (st != GARFIELD_OK) return st;
     return to_status(enqueue_krum_select_mean(x, ds, d, f, m, sel, out, s));
   }
-  st = run_distances_on(plan, base, x, 0, &ds, nullptr, s, kFoldSelect, false);
+  st = run_distances_on(plan, base, x, &ds, s, kFoldSelect);
   if (st != GARFIELD_OK) return st;
   st = to_status(enqueue_krum_select(ds, f, m, sel, s));
   if (st != GARFIELD_OK || !out) return st;
@@ -297,16 +343,8 @@ garfield_status garfield_multikrum_iterated(const float* x, int n, int f, int64_
   if (m <= 0) m = n - f;
   if (m > n - f) return GARFIELD_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  DistSums ds;
-  const bool cs = out && use_colsum(x, n, d, m);
-  void* colsum = nullptr;
-  st = run_distances(x, n, d, colsum_bytes(cs, d), &ds, &colsum, s, kFoldSelect, cs);
-  if (st != GARFIELD_OK) return st;
-  st = to_status(enqueue_krum_rounds(ds, f, m, sel, s));
-  if (st != GARFIELD_OK || !out) return st;
-  if (cs)
-    return to_status(enqueue_mean_complement(x, n, d, sel, m, static_cast<double*>(colsum), out, s));
-  return to_status(enqueue_mean_rows(x, n, d, sel, m, out, s));
+  return select_and_mean(x, n, f, d, m, false, 0, kFoldSelect, sel, out, s,
+                         [&](const DistSums& ds, void*) { return enqueue_krum_rounds(ds, f, m, sel, s); });
 }
 
 garfield_status garfield_median(const float* x, int n, int f, int64_t d, const int32_t* rows,
@@ -347,20 +385,10 @@ garfield_status garfield_mda(const float* x, int n, int f, int64_t d, float* out
   const int64_t subsets = binomial(n, f);
   if (subsets < 0 || subsets > GARFIELD_MDA_MAX_SUBSETS) return GARFIELD_ETOOBIG;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  void* scratch = nullptr;
-  DistSums ds;
-  // scratch: the column sums (if used), then the search's per-block results
-  const bool cs = out && use_colsum(x, n, d, n - f);
-  const size_t cs_bytes = align256(colsum_bytes(cs, d));
   const int fold = mda_uses_cover(n, f) ? kFoldSelect : kFoldMda;
-  st = run_distances(x, n, d, cs_bytes + mda_scratch_bytes(n, f), &ds, &scratch, s, fold, cs);
-  if (st != GARFIELD_OK) return st;
-  st = to_status(enqueue_mda_select(ds, f, static_cast<char*>(scratch) + cs_bytes, sel, s));
-  if (st != GARFIELD_OK || !out) return st;
-  if (cs)
-    return to_status(
-        enqueue_mean_complement(x, n, d, sel, n - f, static_cast<double*>(scratch), out, s));
-  return to_status(enqueue_mean_rows(x, n, d, sel, n - f, out, s));
+  return select_and_mean(
+      x, n, f, d, n - f, true, mda_scratch_bytes(n, f), fold, sel, out, s,
+      [&](const DistSums& ds, void* scratch) { return enqueue_mda_select(ds, f, scratch, sel, s); });
 }
 
 garfield_status garfield_average(const float* x, int n, int64_t d, float* out, void* stream) {
@@ -664,31 +692,24 @@ garfield_status garfield_seg_destroy(garfield_segmented* seg) {
 
 size_t garfield_workspace_bytes(int rule, int n, int f, int64_t d, int m) {
   if (n < 1 || n > GARFIELD_NMAX || f < 0 || d < 0) return 0;
-  // Plan for float-aligned rows, as every accepted input is: the same plan as
-  // every call of the rule with these sizes.
-  const float* narrow = reinterpret_cast<const float*>(uintptr_t{4});
+  // Plan for float-aligned rows and outputs: the same plan as every call of
+  // the rule with these sizes.
+  const float* x = reinterpret_cast<const float*>(uintptr_t{4});
+  const float* out = x + static_cast<int64_t>(n) * d;
   switch (rule) {
     case GARFIELD_RULE_MULTIKRUM:
-    case GARFIELD_RULE_MULTIKRUM_ITERATED: {
-      const int mm = m <= 0 ? n - f : m;
-      return dist_workspace_bytes(plan_distances(n, d, narrow)) +
-             align256(colsum_bytes(use_colsum(narrow, n, d, mm), d));
-    }
-    case GARFIELD_RULE_DIST:
+    case GARFIELD_RULE_MULTIKRUM_ITERATED:
+      return plan_mean(x, n, f, d, m <= 0 ? n - f : m, out, rule == GARFIELD_RULE_MULTIKRUM).bytes();
     case GARFIELD_RULE_KRUM:
+    case GARFIELD_RULE_DIST:
     case GARFIELD_RULE_BULYAN:
-      return dist_workspace_bytes(plan_distances(n, d, narrow));
+      return dist_workspace_bytes(plan_distances(n, d, x));
     case GARFIELD_RULE_MDA: {
       const int64_t subsets = binomial(n, f);
       if (n < 2 * f + 1 || subsets < 0 || subsets > GARFIELD_MDA_MAX_SUBSETS) return 0;
-      return dist_workspace_bytes(plan_distances(n, d, narrow)) +
-             align256(colsum_bytes(use_colsum(narrow, n, d, n - f), d)) +
-             align256(mda_scratch_bytes(n, f));
+      return plan_mean(x, n, f, d, n - f, out, true).bytes() + align256(mda_scratch_bytes(n, f));
     }
-    case GARFIELD_RULE_MEDIAN:
-    case GARFIELD_RULE_AVERAGE:
-      return 0;
-    default:
+    default:  // Median, Average, unknown rules
       return 0;
   }
 }

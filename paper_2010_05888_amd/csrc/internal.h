@@ -28,13 +28,17 @@ struct DistPlan {
   int64_t chunk = 0;       // coordinates per workgroup (tile)
   int64_t tiles = 0;       // workgroups of the distance kernel
   int entries = 0;         // partial sums each tile writes
+  bool ring = false;       // direct engine: rows through an LDS ring, one tile per workgroup
 };
 
 // n <= direct_max_n(): distances by direct differences on VALU; else MFMA Gram.
 int direct_max_n();
 void set_direct_max_n(int n);
 
-DistPlan plan_distances(int n, int64_t d, const float* x);
+// How the direct engine streams long inputs: in its register form always, in
+// its ring form where that is faster (ring_pays), or always in its ring form.
+enum DirectForm { kFormRegisters, kFormAuto, kFormRing };
+DistPlan plan_distances(int n, int64_t d, const float* x, DirectForm form = kFormAuto);
 
 // Compute units of the current device (256 on MI355X; also the fallback when
 // no device is available, e.g. when only planning on a host without a GPU).
@@ -66,8 +70,44 @@ hipError_t enqueue_reference(const float* x, const DistPlan& p, const DistWorksp
 // sum or a sum of some of the rows might not be exact (ColSum in
 // direct_body.h).
 constexpr int kColSumMaxN = 12;
+// mean (ring plans with n <= kGuessMaxN only): see RingMean.
+struct RingMean;
 hipError_t enqueue_distances(const float* x, const DistPlan& p, const DistWorkspace& ws,
-                             hipStream_t s, bool sum_tiles = true, double* colsum = nullptr);
+                             hipStream_t s, bool sum_tiles = true, double* colsum = nullptr,
+                             const RingMean* mean = nullptr);
+
+// The direct engine's ring form (ring_direct.hip) for long inputs: rows
+// through an LDS ring, one persistent workgroup per CU (ring_pays: whether
+// that is the faster form for n rows of d coordinates; ring_stage: coordinates
+// per stage).
+bool ring_pays(int n, int64_t d);
+int ring_stage(int n);
+hipError_t enqueue_distances_ring(const float* x, const DistPlan& p, double* partial,
+                                  const RingMean* mean, hipStream_t s);
+
+// The mean of a selection written by the distance pass itself. enqueue_guess
+// makes Multi-Krum's selection of m rows (f as the rule's) on each of
+// kGuessRuns samples of kGuessRun consecutive coordinates, spread over d, and
+// writes the kGuessRuns masks. Where all of them agree, the distance pass
+// writes the mean of those rows to out (the fp64 sum in ascending row order,
+// rounded once); where they do not, it writes the column sums (colsum, unless
+// null) as the plain step's colsum. enqueue_mean_after then finishes the call
+// once the selection itself is known: nothing is left to do when the guess was
+// right, else it writes the mean from the column sums or from the rows.
+constexpr int kGuessMaxN = 20;
+constexpr int kGuessRuns = 8;
+constexpr int kGuessRun = 1024;
+struct RingMean {
+  const uint64_t* guess;  // kGuessRuns masks (device); null: no guess, as if they disagreed
+  double* colsum;         // d doubles, or null
+  float* out;             // d floats
+  int m;
+};
+bool guess_pays(int n, int64_t d, int f, int m, const float* out);
+hipError_t enqueue_guess(const float* x, int n, int64_t d, int f, int m, uint64_t* guess,
+                         hipStream_t s);
+hipError_t enqueue_mean_after(const float* x, int n, int64_t d, const int32_t* sel,
+                              const RingMean& mean, hipStream_t s);
 // Direct-engine plans with at most kFoldTiles tiles and max_entries entries
 // may leave the tile sums to the selection kernel (DistSums' folded form):
 // its waves add four entries at a time, so a workgroup of w waves folds up to

@@ -9,6 +9,7 @@
 #include "direct_body.h"
 #include "dist_layout.h"
 #include "internal.h"
+#include "krum_mask.h"
 #include "timing.h"
 
 namespace garfield {
@@ -157,56 +158,6 @@ __device__ __forceinline__ void fold_tiles(const double* __restrict__ partial, i
     }
   }
   __syncthreads();
-}
-
-// Multi-Krum's selection from the N x N distances (entry sums esum, direct
-// layout), by the 64 lanes of one wave without LDS traffic or barriers: lane
-// i < N sorts its row's N-1 distances, adds the k = N-f-2 smallest as the
-// butterfly of krum_flags adds them (a balanced tree in ascending order, the
-// other slots 0: the same bits), and ranks its (score, i) against every
-// lane's. Returns the lane-uniform mask of the m selected rows.
-template <int N>
-__device__ __forceinline__ uint64_t krum_mask_wave(const double* esum, int f, int m) {
-  constexpr int M = N - 1;
-  const int i = threadIdx.x & 63;
-  const int k = N - f - 2;
-  double score = 0.0;
-  if (i < N) {
-    double r[M];
-#pragma unroll
-    for (int q = 0; q < M; ++q) {
-      const int j = q < i ? q : q + 1;
-      r[q] = esum[direct_entry(N, i < j ? i : j, i < j ? j : i)];
-    }
-#pragma unroll
-    for (int a = 0; a < M; ++a)  // bubble network: ascending
-#pragma unroll
-      for (int b = 0; b + 1 < M - a; ++b) {
-        const double lo = __builtin_fmin(r[b], r[b + 1]);
-        r[b + 1] = __builtin_fmax(r[b], r[b + 1]);
-        r[b] = lo;
-      }
-    double t[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) t[q] = (q < M && q < k) ? r[q < M ? q : 0] : 0.0;
-#pragma unroll
-    for (int h = 1; h < 16; h <<= 1)
-#pragma unroll
-      for (int q = 0; q < 16; q += 2 * h) t[q] = t[q] + t[q + h];
-    score = t[0];
-  }
-  const int64_t bits = __double_as_longlong(score);
-  const int lo = static_cast<int>(bits), hi = static_cast<int>(bits >> 32);
-  int rank = 0;
-#pragma unroll
-  for (int j = 0; j < N; ++j) {
-    const uint64_t sj_bits =
-        (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(hi, j))) << 32) |
-        static_cast<uint32_t>(__builtin_amdgcn_readlane(lo, j));
-    const double sj = __longlong_as_double(static_cast<int64_t>(sj_bits));
-    rank += (sj < score) | ((sj == score) & (j < i));
-  }
-  return __ballot(i < N && rank < m);
 }
 
 template <int N>
@@ -951,7 +902,7 @@ bool fused_enabled() { return __atomic_load_n(&g_fused, __ATOMIC_RELAXED); }
 void set_fused(bool on) { __atomic_store_n(&g_fused, on, __ATOMIC_RELAXED); }
 
 bool krum_fusable(const DistPlan& p, const float* out) {
-  if (!fused_enabled() || p.engine != kEngineDirect || p.n < 3 || p.n > kFusedMaxN ||
+  if (!fused_enabled() || p.engine != kEngineDirect || p.ring || p.n < 3 || p.n > kFusedMaxN ||
       p.width != 4 || p.tiles > kFoldTiles || !out || load_width(out) != 4)
     return false;
   // every workgroup reads all tile partials: keep that repeated read small

@@ -1,0 +1,150 @@
+"""The direct engine's ring form (long inputs of up to 20 rows) and the mean it
+writes on a guessed selection, at the smallest lengths that take it: whole and
+ragged last stages, every split of the pairs over wave groups, and the three
+ways a guess can end (right, the samples disagree, all of them wrong)."""
+import itertools
+
+import pytest
+import torch
+
+import paper_2010_05888_amd as gf
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _least(n):
+    return 1 << (21 if n >= 16 else 23 if n >= 9 else 24)
+
+
+def _rows(n, d, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    return torch.randn((n, d), device=DEV, generator=g)
+
+
+def _dist64(x):
+    n, d = x.shape
+    D = torch.zeros((n, n), dtype=torch.float64, device=DEV)
+    for a in range(0, d, 1 << 20):
+        c = x[:, a:a + (1 << 20)].double()
+        for i in range(n):
+            D[i] += (c - c[i]).square_().sum(1)
+    return D
+
+
+def _kernels(call):
+    gf.set_kernel_timing(True)
+    out = call()
+    torch.cuda.synchronize()
+    names = set(gf.kernel_timing())
+    gf.set_kernel_timing(False)
+    return out, names
+
+
+# every group count and pair split, stages of 1,024 and 512 coordinates; the
+# last stage empty, of one coordinate, and one coordinate short of whole
+@pytest.mark.parametrize("n,extra", [(2, 0), (8, 1), (9, 1023), (10, 0), (11, 511), (12, 1),
+                                     (13, 0), (14, 511), (15, 1), (16, 0), (17, 1), (18, 511),
+                                     (19, 0), (20, 1)])
+def test_distances(n, extra):
+    d = _least(n) + extra
+    x = _rows(n, d, 100 * n + extra)
+    x[n - 1] = x[0]  # equal rows, in different groups
+    D, names = _kernels(lambda: gf.pairwise_sqdist(x))
+    assert "dist_ring" in names
+    W = _dist64(x)
+    # a rounded difference and at most 16 fp32 multiply-adds per lane and run,
+    # fp64 beyond: 18 * 2^-24 of a sum of positive terms
+    assert bool(((D - W).abs() <= 18 * 2.0 ** -24 * W).all())
+    assert torch.equal(D, D.T) and D[0, n - 1].item() == 0.0
+    others = list(range(1, n - 1))
+    assert torch.equal(D[0, others], D[n - 1, others])
+    # whichever groups the pairs fall in, their sums are formed alike
+    perm = torch.randperm(n, generator=torch.Generator().manual_seed(n)).to(DEV)
+    assert torch.equal(gf.pairwise_sqdist(x[perm].contiguous()), D[perm][:, perm])
+
+
+def _krum(D, f, m):
+    n = len(D)
+    scores = sorted((sum(sorted(D[i][j] for j in range(n) if j != i)[:n - f - 2]), i)
+                    for i in range(n))
+    return sorted(i for _, i in scores[:m])
+
+
+def _mda(D, f):
+    n = len(D)
+    return list(min(itertools.combinations(range(n), n - f),
+                    key=lambda s: max(D[i][j] for i in s for j in s)))
+
+
+def _mean64(x, rows):
+    acc = torch.zeros(x.shape[1], dtype=torch.float64, device=DEV)
+    for r in rows:
+        acc += x[r].double()
+    return (acc / len(rows)).float()
+
+
+# m beside the default: with n <= 12 and 2m > n + 4 a disagreement leaves the
+# column sums, otherwise nothing
+@pytest.mark.parametrize("ends", ["right", "disagree", "wrong"])
+@pytest.mark.parametrize("rule,n,f,m,extra", [
+    ("multikrum", 3, 0, 3, 0), ("multikrum", 7, 1, 6, 1023), ("multikrum", 11, 2, 9, 511),
+    ("multikrum", 11, 2, 7, 1), ("multikrum", 12, 2, 10, 0), ("mda", 10, 3, 7, 1),
+    ("multikrum", 13, 2, 11, 511), ("mda", 16, 2, 14, 0), ("multikrum", 18, 4, 14, 1),
+    ("multikrum", 20, 4, 16, 511)])
+def test_mean_on_a_guess(rule, n, f, m, extra, ends):
+    d = (1 << 23) + extra
+    x = _rows(n, d, 7 * n + m)
+    out_rows = list(range(1, 1 + n - m))  # to be left out
+    if ends != "disagree":
+        for r in out_rows:
+            x[r] *= 30.0 + r
+    else:
+        # values 2^30 apart in some coordinates: their column sums are not exact
+        for r in range(n):
+            x[r, 1001 * r::1001 * n] *= 2.0 ** 30
+    if ends == "wrong" and out_rows:
+        # every sample (1,024 coordinates from r * (d // 8) on) shows others
+        for r in range(8):
+            a = r * (d // 8)
+            w = x[:, a:a + 1024]
+            w[out_rows] /= torch.tensor([30.0 + q for q in out_rows], device=DEV)[:, None]
+            w[[n - 1 - i for i in range(len(out_rows))]] *= 100.0
+    kw = {} if rule == "mda" else {"m": m}
+    (out, sel), names = _kernels(lambda: getattr(gf, rule)(x, f, **kw))
+    assert {"guess", "dist_ring_mean", "mean_after"} <= names
+    D = _dist64(x).tolist()
+    want = _mda(D, f) if rule == "mda" else _krum(D, f, m)
+    assert sel.tolist() == want
+    if ends != "disagree":
+        assert want == [i for i in range(n) if i not in out_rows]
+    assert torch.equal(out, _mean64(x, want))  # bit for bit: the same fp64 sum, rounded once
+
+
+def test_column_sums_without_a_guess():
+    """The iterated rule's selection is never guessed; with n <= 12 its mean
+    takes the column sums, the selected rows' sum where those are not exact."""
+    n, f, m, d = 11, 2, 9, (1 << 23) + 257
+    x = _rows(n, d, 5)
+    x[3] *= 2.0
+    x[4, ::1001] *= 2.0 ** 30
+    (out, sel), names = _kernels(lambda: gf.multikrum_iterated(x, f, m))
+    assert {"dist_ring_mean", "mean_complement"} <= names and "guess" not in names
+    assert torch.equal(out, _mean64(x, sel.tolist()))
+
+
+def test_out_inside_the_input_is_not_guessed():
+    """A caller that lets the aggregate overwrite one of its rows gets the mean
+    of the rows as they were, also where samples would mislead a guess."""
+    import ctypes
+    n, f, d = 11, 2, 1 << 23
+    x = _rows(n, d, 9)
+    x[5] *= 40.0
+    x[6] *= 50.0
+    want = _mean64(x, [i for i in range(n) if i not in (5, 6)])
+    sel = torch.empty(n - f, dtype=torch.int32, device=DEV)
+    s = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    p = [ctypes.c_void_p(t.data_ptr()) for t in (x, x[2], sel)]
+    code, names = _kernels(lambda: gf.load().garfield_multikrum(p[0], n, f, d, 0, p[1], p[2], s))
+    assert code == gf.OK and "guess" not in names
+    assert torch.equal(x[2], want)
