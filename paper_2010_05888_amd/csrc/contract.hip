@@ -155,6 +155,272 @@ __global__ __launch_bounds__(kBlock) void k_median_nodes(const float* __restrict
   }
 }
 
+// ---------------------------------------------------------------------------
+// Few rows (n <= kSharedMaxRows): what the nodes share is done once per
+// coordinate, from registers. A workgroup stages kSharedCoords coordinates of
+// all N rows in LDS and every lane takes two of them, so each output row is
+// written in 512-byte runs per wave.
+//
+// Mean: the lane converts its N values to fp64 once and, for every node, adds
+// the rows in ascending order, each times 1 or 0 as the node's mask says (an
+// exact product; the weights are scalars formed beside the vector work). The
+// form above reads every listed value from LDS again, with its offset, and
+// converts it: 28 LDS reads and 42 vector instructions per node of 14 rows,
+// against 20 multiply-adds here at N = 20. (A uniform branch per row in place
+// of the weight took 711 us where this takes 420 and the form above 548: n = 20
+// nodes of 11.2 M coordinates, 14 rows each.)
+//
+// Median: the lane sorts its N values once, and a node that hears all but X of
+// them takes the middle of what is left when its X absent values are removed
+// from the sorted row: with those in ascending order e[1..X], the rank-t value
+// of the rest is s[t] if e[1] > s[t], else s[t + 1] if e[2] > s[t + 1], and so
+// on. X LDS reads, a sort of X values and 2 X selects per node and rank, where
+// the network over q values took q reads and about 6 q instructions: 827 -> 410
+// us for n = 20 nodes of 11.2 M coordinates and 17 peers.
+//
+// Both then run at 4.3 TB/s of rows read and rows written, the rate of a copy
+// on this chip (4.6).
+//
+// A node whose list repeats a row (its mask has fewer rows) takes its listed
+// rows in order, and so does the mean of a wave that holds an infinity or NaN
+// (a weight of 0 would not leave those out).
+constexpr int kSharedMaxRows = 32;
+constexpr int kSharedCoords = 2 * kBlock;
+constexpr int kSharedMaxAbsent = 6;
+constexpr int64_t kSharedMinCoords = int64_t{1} << 18;  // two workgroups per CU
+
+// Coordinates c0 .. c0 + kSharedCoords - 1 of all N rows into LDS, row r at
+// tile[r * kSharedCoords]; those at or beyond d read as 0. Wave w loads 1 KB
+// pieces w, w + 4, ..., all of them before any store to LDS. No barrier.
+template <int N>
+__device__ __forceinline__ void stage_rows(const float* __restrict__ x, int64_t d, int64_t c0,
+                                           float* __restrict__ tile) {
+  constexpr int PARTS = kSharedCoords / 256, TOTAL = N * PARTS, PER = (TOTAL + 3) / 4;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (c0 + kSharedCoords <= d) {  // uniform: a whole tile
+    f4 v[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int j = wave + 4 * u;  // wave-uniform
+      if (u < TOTAL / 4 || j < TOTAL)
+        v[u] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(
+            x + static_cast<int64_t>(j / PARTS) * d + c0 + (j % PARTS) * 256 + 4 * lane));
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int j = wave + 4 * u;
+      if (u < TOTAL / 4 || j < TOTAL) *reinterpret_cast<f4*>(tile + j * 256 + 4 * lane) = v[u];
+    }
+  } else {
+    for (int i = threadIdx.x; i < N * kSharedCoords; i += kBlock) {
+      const int64_t c = c0 + i % kSharedCoords;
+      tile[i] = c < d ? x[static_cast<int64_t>(i / kSharedCoords) * d + c] : 0.0f;
+    }
+  }
+}
+
+__device__ __forceinline__ void store_pair(float* __restrict__ row, int64_t c, int64_t d, float a,
+                                           float b) {
+  const float o[2] = {a, b};
+  if (c + 2 <= d) store_w<2>(row + c, o);
+  else if (c < d) row[c] = a;
+}
+
+template <int N>
+__global__ __launch_bounds__(kBlock) void k_mean_shared(const float* __restrict__ x, int64_t d,
+                                                        int nodes,
+                                                        const int32_t* __restrict__ rows, int k,
+                                                        float* __restrict__ y) {
+  __shared__ __attribute__((aligned(16))) float tile[N * kSharedCoords];
+  __shared__ uint32_t masks[kNmax];  // 0: the node's list repeats a row
+  const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kSharedCoords;
+  if (static_cast<int>(threadIdx.x) < nodes) {
+    uint32_t m = 0;
+    for (int i = 0; i < k; ++i) m |= 1u << row_of(rows + threadIdx.x * k, i, N);
+    masks[threadIdx.x] = __builtin_popcount(m) == k ? m : 0;
+  }
+  stage_rows<N>(x, d, c0, tile);
+  __syncthreads();
+  const int64_t c = c0 + 2 * threadIdx.x;
+  double a[N], b[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const f2 t = *reinterpret_cast<const f2*>(tile + i * kSharedCoords + 2 * threadIdx.x);
+    a[i] = static_cast<double>(t.x);
+    b[i] = static_cast<double>(t.y);
+  }
+  double z = 0.0;  // NaN if any value is not finite
+#pragma unroll
+  for (int i = 0; i < N; ++i) z = __builtin_fma(a[i], 0.0, __builtin_fma(b[i], 0.0, z));
+  const bool finite = __ballot(__builtin_isnan(z)) == 0;
+  const double count = static_cast<double>(k), inv = 1.0 / count;
+  for (int v = 0; v < nodes; ++v) {
+    const uint32_t m = __builtin_amdgcn_readfirstlane(masks[v]);
+    double s0 = 0.0, s1 = 0.0;
+    if (m && finite) {  // uniform
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const double w = (m >> i) & 1 ? 1.0 : 0.0;
+        s0 = __builtin_fma(a[i], w, s0);
+        s1 = __builtin_fma(b[i], w, s1);
+      }
+    } else {
+      for (int i = 0; i < k; ++i) {
+        const float* p = tile + row_of(rows + v * k, i, N) * kSharedCoords + 2 * threadIdx.x;
+        s0 += static_cast<double>(p[0]);
+        s1 += static_cast<double>(p[1]);
+      }
+    }
+    store_pair(y + static_cast<int64_t>(v) * d, c, d, static_cast<float>(mean_of(s0, count, inv)),
+               static_cast<float>(mean_of(s1, count, inv)));
+  }
+}
+
+// The rank-T value of the N sorted values s (rank r at s[Net::reg(r)]) without
+// the X values e (ascending).
+template <int N, int X, int T>
+__device__ __forceinline__ float rank_without(const float* s, const float* e) {
+  using Net = SortNet<N>;
+  float r = s[Net::reg(T + X)];
+#pragma unroll
+  for (int k = X - 1; k >= 0; --k) {
+    const float at = s[Net::reg(T + k)];
+    r = e[k] <= at ? r : at;
+  }
+  return r;
+}
+
+// The median of the N - X values left of s (as above).
+template <int N, int X>
+__device__ __forceinline__ float median_without(const float* s, float* e) {
+  constexpr int Q = N - X;
+  if constexpr (X >= 2) {
+    float t[X];
+#pragma unroll
+    for (int k = 0; k < X; ++k) t[k] = e[k];
+    SortNet<X>::run(t);
+#pragma unroll
+    for (int k = 0; k < X; ++k) e[k] = t[SortNet<X>::reg(k)];
+  }
+  const float lo = rank_without<N, X, (Q - 1) / 2>(s, e);
+  if constexpr (Q % 2 == 1) {
+    return lo;
+  } else {  // mean of the two middle values, exact in fp64, rounded once
+    const float hi = rank_without<N, X, Q / 2>(s, e);
+    return static_cast<float>((static_cast<double>(lo) + static_cast<double>(hi)) * 0.5);
+  }
+}
+
+template <int N, int X>
+__global__ __launch_bounds__(kBlock) void k_median_shared(const float* __restrict__ x, int64_t d,
+                                                          int nodes,
+                                                          const int32_t* __restrict__ rows,
+                                                          float* __restrict__ y) {
+  constexpr int Q = N - X;
+  constexpr int XP = X <= 4 ? 4 : 8;  // offsets per node, read 16 bytes at a time
+  __shared__ __attribute__((aligned(16))) float tile[N * kSharedCoords];
+  __shared__ __attribute__((aligned(16))) int32_t absent[kNmax * XP];  // offsets into tile
+  __shared__ int whole[kNmax];  // the node's list holds Q rows
+  const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kSharedCoords;
+  if (static_cast<int>(threadIdx.x) < nodes) {
+    uint32_t m = 0;
+    for (int i = 0; i < Q; ++i) m |= 1u << row_of(rows + threadIdx.x * Q, i, N);
+    const bool ok = __builtin_popcount(m) == Q;
+    whole[threadIdx.x] = ok;
+    uint32_t rest = ok ? ~m & (N == 32 ? ~0u : (1u << N) - 1) : 0;
+    for (int k = 0; k < XP; ++k, rest &= rest - 1)
+      absent[threadIdx.x * XP + k] = rest ? __builtin_ctz(rest) * kSharedCoords : 0;
+  }
+  stage_rows<N>(x, d, c0, tile);
+  __syncthreads();
+  const int64_t c = c0 + 2 * threadIdx.x;
+  const float* mine = tile + 2 * threadIdx.x;
+  float s0[N], s1[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const f2 t = *reinterpret_cast<const f2*>(mine + i * kSharedCoords);
+    s0[i] = t.x;
+    s1[i] = t.y;
+  }
+  SortNet<N>::run(s0);
+  SortNet<N>::run(s1);
+  for (int v = 0; v < nodes; ++v) {
+    float o0, o1;
+    if (__builtin_amdgcn_readfirstlane(whole[v])) {
+      float e0[X > 0 ? X : 1], e1[X > 0 ? X : 1];
+#pragma unroll
+      for (int k = 0; k < X; ++k) {
+        const f2 t = *reinterpret_cast<const f2*>(mine + absent[v * XP + k]);
+        e0[k] = t.x;
+        e1[k] = t.y;
+      }
+      o0 = median_without<N, X>(s0, e0);
+      o1 = median_without<N, X>(s1, e1);
+    } else {
+      using Net = MedianNet<Q>;
+      float a[Q], b[Q];
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        const float* p = mine + row_of(rows + v * Q, i, N) * kSharedCoords;
+        a[i] = p[0];
+        b[i] = p[1];
+      }
+      Net::run(a);
+      Net::run(b);
+      if constexpr (Q % 2 == 1) {
+        o0 = a[Net::LO];
+        o1 = b[Net::LO];
+      } else {
+        o0 = static_cast<float>((static_cast<double>(a[Net::LO]) + static_cast<double>(a[Net::HI])) * 0.5);
+        o1 = static_cast<float>((static_cast<double>(b[Net::LO]) + static_cast<double>(b[Net::HI])) * 0.5);
+      }
+    }
+    store_pair(y + static_cast<int64_t>(v) * d, c, d, o0, o1);
+  }
+}
+
+unsigned shared_grid(int64_t d) {
+  return static_cast<unsigned>((d + kSharedCoords - 1) / kSharedCoords);
+}
+
+template <int N>
+hipError_t mean_shared_dispatch(const float* x, int n, int64_t d, int nodes, const int32_t* rows,
+                                int k, float* y, hipStream_t s) {
+  if constexpr (N > kSharedMaxRows) {
+    return hipErrorInvalidValue;
+  } else {
+    if (n != N) return mean_shared_dispatch<N + 1>(x, n, d, nodes, rows, k, y, s);
+    launch("mean_nodes", k_mean_shared<N>, dim3(shared_grid(d)), dim3(kBlock), 0, s, x, d, nodes,
+           rows, k, y);
+    return hipGetLastError();
+  }
+}
+
+template <int N, int X>
+hipError_t median_shared_absent(const float* x, int64_t d, int nodes, const int32_t* rows, int q,
+                                float* y, hipStream_t s) {
+  if constexpr (X > kSharedMaxAbsent || 3 * X >= N) {
+    return hipErrorInvalidValue;
+  } else {
+    if (q != N - X) return median_shared_absent<N, X + 1>(x, d, nodes, rows, q, y, s);
+    launch("median_nodes", k_median_shared<N, X>, dim3(shared_grid(d)), dim3(kBlock), 0, s, x, d,
+           nodes, rows, y);
+    return hipGetLastError();
+  }
+}
+
+template <int N>
+hipError_t median_shared_dispatch(const float* x, int n, int64_t d, int nodes,
+                                  const int32_t* rows, int q, float* y, hipStream_t s) {
+  if constexpr (N > kSharedMaxRows) {
+    return hipErrorInvalidValue;
+  } else {
+    if (n != N) return median_shared_dispatch<N + 1>(x, n, d, nodes, rows, q, y, s);
+    return median_shared_absent<N, 0>(x, d, nodes, rows, q, y, s);
+  }
+}
+
 unsigned tile_grid(int64_t d) {
   return static_cast<unsigned>((d + kTileCoords - 1) / kTileCoords);
 }
@@ -212,8 +478,15 @@ hipError_t bulyan_nodes_dispatch(int theta, int beta, const float* x, int n, int
 }  // namespace
 
 hipError_t enqueue_mean_nodes(const float* x, int n, int64_t d, int nodes, const int32_t* rows,
-                              int k, float* y, hipStream_t s) {
+                              int k, bool ascending, float* y, hipStream_t s) {
   if (d == 0 || nodes == 0) return hipSuccess;
+  // Against the form below, whose work per node grows with k where the shared
+  // form's grows with n: 1.1 to 1.3 times as fast with k near n (n = 9 to 32,
+  // d = 10^6 and 8 * 10^6), 0.83 with k = 1 of n = 32, 0.96 to 1.03 with k = 1 of
+  // n = 24. Short rows would leave its larger tiles too few workgroups (d = 10^5:
+  // 0.8 to 1.04).
+  if (ascending && n <= kSharedMaxRows && 4 * k + 16 >= n && d >= kSharedMinCoords)
+    return mean_shared_dispatch<1>(x, n, d, nodes, rows, k, y, s);
   launch("mean_nodes", k_mean_nodes, dim3(tile_grid(d)), dim3(kBlock),
          static_cast<uint32_t>(tile_bytes(n, nodes * k)), s, x, n, d, nodes, rows, k, y);
   return hipGetLastError();
@@ -222,6 +495,11 @@ hipError_t enqueue_mean_nodes(const float* x, int n, int64_t d, int nodes, const
 hipError_t enqueue_median_nodes(const float* x, int n, int64_t d, int nodes, const int32_t* rows,
                                 int k, float* y, hipStream_t s) {
   if (d == 0 || nodes == 0) return hipSuccess;
+  // Against the network over each node's k values: 1.2 times as fast at n = 9
+  // with 2 absent, 2.2 at n = 24 with 5, 3.6 at n = 32 with 3; 0.9 to 0.97 at
+  // n = 16 with 6.
+  if (n <= kSharedMaxRows && n - k <= kSharedMaxAbsent && 3 * (n - k) < n && d >= kSharedMinCoords)
+    return median_shared_dispatch<1>(x, n, d, nodes, rows, k, y, s);
   return median_nodes_dispatch<1>(k, x, n, d, nodes, rows, y, s);
 }
 

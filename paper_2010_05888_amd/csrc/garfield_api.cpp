@@ -494,7 +494,7 @@ garfield_status garfield_contract_step(int rule, const float* x, int n, int64_t 
   if (rule == GARFIELD_RULE_MEDIAN)
     return to_status(enqueue_median_nodes(x, n, d, n, peers, q, y, s));
   if (rule == GARFIELD_RULE_AVERAGE)
-    return to_status(enqueue_mean_nodes(x, n, d, n, peers, q, y, s));
+    return to_status(enqueue_mean_nodes(x, n, d, n, peers, q, false, y, s));
   DistSums ds;
   void* scratch = nullptr;
   st = run_distances(x, n, d, static_cast<size_t>(n) * k * sizeof(int32_t), &ds, &scratch, s);
@@ -506,7 +506,7 @@ garfield_status garfield_contract_step(int rule, const float* x, int n, int64_t 
                  : enqueue_peer_select(ds, n, peers, q, f, m, rounds, k, sel, s);
   if (e != hipSuccess) return to_status(e);
   if (rule == GARFIELD_RULE_BULYAN) return to_status(enqueue_bulyan_nodes(x, n, d, n, q, f, sel, y, s));
-  return to_status(enqueue_mean_nodes(x, n, d, n, sel, k, y, s));
+  return to_status(enqueue_mean_nodes(x, n, d, n, sel, k, true, y, s));
 }
 
 garfield_status garfield_seg_create(int rule, int n, int f, int m, garfield_segmented** out) {

@@ -185,8 +185,10 @@ hipError_t enqueue_peer_select(const DistSums& ds, int nodes, const int32_t* pee
 // of q-f peers (C(q, f) subsets searched by one workgroup), ascending.
 hipError_t enqueue_peer_mda(const DistSums& ds, int nodes, const int32_t* peers, int q, int f,
                             int32_t* sel, hipStream_t s);
+// ascending: every node's list is in ascending row order (the sum's order is
+// the list's).
 hipError_t enqueue_mean_nodes(const float* x, int n, int64_t d, int nodes, const int32_t* rows,
-                              int k, float* y, hipStream_t s);
+                              int k, bool ascending, float* y, hipStream_t s);
 hipError_t enqueue_median_nodes(const float* x, int n, int64_t d, int nodes, const int32_t* rows,
                                 int k, float* y, hipStream_t s);
 hipError_t enqueue_bulyan_nodes(const float* x, int n, int64_t d, int nodes, int q, int f,

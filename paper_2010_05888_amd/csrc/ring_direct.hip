@@ -191,8 +191,9 @@ __device__ __forceinline__ void ring_write(const RingOut& o, uint64_t mask, cons
         s1 += static_cast<double>(v[i].y);
       }
     }
-    const double count = static_cast<double>(o.m);
-    const float r[2] = {static_cast<float>(s0 / count), static_cast<float>(s1 / count)};
+    const double count = static_cast<double>(o.m), inv = 1.0 / count;
+    const float r[2] = {static_cast<float>(mean_of(s0, count, inv)),
+                        static_cast<float>(mean_of(s1, count, inv))};
     if constexpr (FULL) {
       store_w<2>(o.out + c, r);
     } else {

@@ -165,3 +165,48 @@ def test_mda_small_integer_ties():
         got = y.cpu().numpy()
         for v in range(n):  # exact sums of small integers: equal iff the same rows were taken
             assert np.array_equal(got[v], want[v]), (trial, n, q, f, v, want_sel[v])
+
+
+# the forms that share a coordinate's rows between the nodes, from 2^18
+# coordinates on: n at both sides of their limit of 32 rows, every count of
+# absent rows up to and past 6, whole and ragged tiles of 512 coordinates
+@pytest.mark.parametrize("n,absent,extra", [(1, 0, 1), (3, 0, 0), (4, 1, 1), (8, 2, 511),
+                                            (10, 3, 510), (13, 4, 2), (20, 5, 513), (19, 6, 2),
+                                            (18, 6, 3), (32, 6, 1025), (32, 7, 188), (32, 0, 511),
+                                            (33, 3, 188)])
+def test_shared_rows(n, absent, extra):
+    d = (1 << 18) + extra
+    q = n - absent
+    rng, x = _inputs(n, d, 7 * n + absent)
+    peers = np.stack([rng.permutation(n)[:q] for _ in range(n)]).astype(np.int32)
+    if q > 1:
+        peers[0, q - 1] = peers[0, 0]  # a list that repeats a row: the general form
+    xt, pt = torch.from_numpy(x).to(DEV), torch.from_numpy(peers).to(DEV)
+    got = gf.contract_step("median", xt, pt, 0).cpu().numpy()
+    srt = np.sort(x[peers].astype(np.float64), axis=1)
+    want = ((srt[:, (q - 1) // 2] + srt[:, q // 2]) / 2).astype(np.float32)
+    assert np.array_equal(got, want)
+    if q < 3:
+        return
+    # Multi-Krum of all q rows: the selection is the list, in ascending order
+    # (a list that repeats a row has no such selection)
+    got = gf.contract_step("multikrum", xt, pt, 0, q).cpu().numpy()
+    for v in range(1, n):
+        acc = np.zeros(d)
+        for r in np.sort(peers[v]):
+            acc += x[r].astype(np.float64)
+        assert np.array_equal(got[v], (acc / q).astype(np.float32)), v
+
+
+def test_shared_mean_leaves_out_what_is_not_finite():
+    n, q, d = 12, 9, 1 << 18
+    rng, x = _inputs(n, d, 3)
+    x[11, 700] = np.inf
+    x[10, 40] = np.nan
+    peers = np.tile(np.arange(q, dtype=np.int32), (n, 1))  # nobody hears rows 9 to 11
+    y = gf.contract_step("multikrum", torch.from_numpy(x).to(DEV), torch.from_numpy(peers).to(DEV),
+                         0, q).cpu().numpy()
+    acc = np.zeros(d)
+    for r in range(q):
+        acc += x[r].astype(np.float64)
+    assert np.array_equal(y, np.tile((acc / q).astype(np.float32), (n, 1)))
