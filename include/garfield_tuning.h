@@ -39,8 +39,8 @@ int garfield_tuning_set_direct_max_n(int n);
 int garfield_tuning_set_fused(int on);
 
 /*
- * MDA's search: from this many candidate subsets C(n, f) on (default 2^20),
- * the least diameter and the lexicographically first subset attaining it are
+ * MDA's search: from this many candidate subsets C(n, f) on (the default, 2^20,
+ * leaves the line to the library, which draws it at 2^13), the least diameter and the lexicographically first subset attaining it are
  * found through vertex covers of the graph of pairs farther apart than a
  * threshold (one workgroup; work grows with 2^f, not with C(n, f)); below it
  * every subset is enumerated. Both give the same subset. Returns the previous

@@ -290,6 +290,22 @@ __global__ __launch_bounds__(kSelectThreads) void k_bulyan_select(DistSums ds, i
   write_selected(krum_rounds_mask(D, order, pos, n, f, rounds), n, nullptr, sel);
 }
 
+// The distances among the q rows of `list` (clamped into the input) into an
+// LDS q x q array, and the rows themselves into map.
+__device__ void gather_peers(const DistSums& ds, const int32_t* __restrict__ list, int q, double* D,
+                             int32_t* map) {
+  if (static_cast<int>(threadIdx.x) < q) {
+    const int r = list[threadIdx.x];
+    map[threadIdx.x] = r < 0 ? 0 : (r >= ds.n ? ds.n - 1 : r);
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < q * q; idx += blockDim.x) {
+    const int a = idx / q, b = idx % q;
+    D[idx] = a == b ? 0.0 : dist_entry(ds, map[a], map[b]);
+  }
+  __syncthreads();
+}
+
 // Contraction (many nodes, each aggregating its peers): workgroup v gathers the
 // distances among its q peers (peers[v*q .. v*q+q-1], rows of the N-row input
 // whose distance sums are ds) into LDS and selects among them, ties going to
@@ -307,16 +323,7 @@ __global__ __launch_bounds__(kBlock) void k_peer_select(DistSums ds,
   __shared__ int flag[kNmax];
   __shared__ int32_t map[kNmax];
   const int v = blockIdx.x;
-  if (static_cast<int>(threadIdx.x) < q) {
-    const int r = peers[static_cast<int64_t>(v) * q + threadIdx.x];
-    map[threadIdx.x] = r < 0 ? 0 : (r >= ds.n ? ds.n - 1 : r);
-  }
-  __syncthreads();
-  for (int idx = threadIdx.x; idx < q * q; idx += blockDim.x) {
-    const int a = idx / q, b = idx % q;
-    D[idx] = a == b ? 0.0 : dist_entry(ds, map[a], map[b]);
-  }
-  __syncthreads();
+  gather_peers(ds, peers + static_cast<int64_t>(v) * q, q, D, map);
   rank_rows(D, q, order, pos);
   int32_t* out = sel + static_cast<int64_t>(v) * kout;
   if (rounds > 0) {
@@ -586,7 +593,8 @@ __global__ __launch_bounds__(kBlock) void k_mda_search(DistSums ds, int s, int64
   }
 }
 
-constexpr int64_t kPeerBoundMinPer = 4;
+constexpr int64_t kPeerCoverMin = 256;
+static_assert(kPeerCoverMin <= kBlock, "a thread per subset");
 
 // Contraction with MDA: workgroup v searches the C(q, f) subsets of its q
 // peers (positions in the peer list, distances gathered as k_peer_select
@@ -603,27 +611,12 @@ __global__ __launch_bounds__(kBlock) void k_peer_mda(DistSums ds, const int32_t*
   const int v = blockIdx.x, s = q - f;
   const ScanLds sl = carve_scan_lds(lds, q, s);
   double* D = sl.D;
-  if (static_cast<int>(threadIdx.x) < q) {
-    const int r = peers[static_cast<int64_t>(v) * q + threadIdx.x];
-    map[threadIdx.x] = r < 0 ? 0 : (r >= ds.n ? ds.n - 1 : r);
-  }
-  __syncthreads();
-  for (int idx = threadIdx.x; idx < q * q; idx += blockDim.x) {
-    const int a = idx / q, b = idx % q;
-    D[idx] = a == b ? 0.0 : dist_entry(ds, map[a], map[b]);
-  }
-  __syncthreads();
-  const int64_t per = (total + kBlock - 1) / kBlock;
-  const int64_t r0 = static_cast<int64_t>(threadIdx.x) * per;
-  const int64_t r1 = (r0 + per < total) ? r0 + per : total;
-  // one workgroup per node: with a few subsets per thread the seed and the
-  // shared bound cost more than they prune
-  __shared__ unsigned long long bound;
-  unsigned long long* bp = per > kPeerBoundMinPer ? &bound : nullptr;
-  if (bp) init_bound(D, q, s, true, bp);
+  gather_peers(ds, peers + static_cast<int64_t>(v) * q, q, D, map);
+  // at most kPeerCoverMin - 1 subsets: one per thread, nothing to prune
+  const int64_t r0 = threadIdx.x, r1 = r0 < total ? r0 + 1 : r0;
   double best = __builtin_inf();
   int64_t best_r = INT64_MAX;
-  mda_scan(D, q, s, r0, r1, sl.idx, sl.pm, bp, &best, &best_r);
+  mda_scan(D, q, s, r0, r1, sl.idx, sl.pm, nullptr, &best, &best_r);
   block_min_pair(rd, rr, &best, &best_r);
   __shared__ unsigned char win[kNmax];
   if (threadIdx.x == 0) unrank_subset(best_r, q, s, win);
@@ -681,172 +674,269 @@ __global__ __launch_bounds__(kBlock) void k_mda_pick(const double* __restrict__ 
 // it touch every pair farther apart than delta: they form a vertex cover of
 // the graph of those pairs. So the least diameter delta* is the smallest pair
 // distance (or 0) whose "farther than" graph has a vertex cover of at most f
-// vertices -- a binary search over the distances sorted in descending order
-// -- and the winner, the lexicographically first subset of diameter delta*,
-// is built vertex by vertex: v joins S (its far neighbours leave it) whenever
-// the vertices still undecided can then be covered within what is left of the
-// budget, else v leaves. Including the smallest possible vertex at every step
-// gives the lexicographically first subset, and every step keeps a completion
-// of exactly s vertices available, so the result is the enumeration's.
+// vertices -- a search over the distances sorted in descending order -- and the
+// winner, the lexicographically first subset of diameter delta*, is built from
+// a cover: going up the vertices, one that the cover leaves out joins S (the
+// cover shows that S can be completed), and one in the cover joins instead
+// whenever some other cover allows it, which then takes the first one's place;
+// else it leaves. Including the smallest possible vertex at every step gives
+// the lexicographically first subset, so the result is the enumeration's.
+//
+// One workgroup of 16 waves; a wave decides a cover by itself (wave_cover), so
+// 16 thresholds are tested at a time, and all vertices of the present cover
+// (at most f <= 16 under the entry points' limit on C(n, f); any more take
+// another turn) at once, each under the assumption that those before it leave:
+// the first that may join ends that assumption. It is bound by latency: n = 39,
+// f = 9 40 us, n = 64, f = 7 54 us, n = 33, f = 16 45 us, on N(0, 1) rows. (The
+// search tree's 2^f paths spread over the workgroup, one threshold and one
+// vertex at a time, took 303, 1,694 and 517.)
 constexpr int kCoverThreads = 1024;
+constexpr int kCoverWaves = kCoverThreads / 64;
+constexpr int kCoverStack = kNmax;  // pending branches of wave_cover: one per lane
 
 __device__ __forceinline__ uint64_t low_bits(int n) {
   return n >= 64 ? ~uint64_t{0} : (uint64_t{1} << n) - 1;
 }
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
+  return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+__device__ __forceinline__ uint64_t lane64(uint64_t v, int lane) {  // lane: uniform
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(v), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(v >> 32), lane);
+  return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+extern "C" __device__ __attribute__((const)) unsigned int __ockl_wfred_max_u32(unsigned int);
+extern "C" __device__ __attribute__((const)) unsigned int __ockl_wfred_add_u32(unsigned int);
 
-// One root-to-leaf path of the bounded search tree for a cover of at most k
-// more vertices than c: at step t the first uncovered pair (u, v) (u the
-// lowest vertex with an uncovered pair, v its lowest such neighbour) puts v
-// in the cover if bit t of `path` is set, else u. True if the path covers
-// every pair.
-__device__ bool cover_path(const uint64_t* adj, uint64_t U, uint64_t c, int k, int64_t path) {
-  for (int step = 0;; ++step) {
-    int u = -1;
-    uint64_t nb = 0;
-    for (uint64_t cand = U & ~c; cand; cand &= cand - 1) {
-      const int w = __builtin_ctzll(cand);
-      const uint64_t e = adj[w] & ~c;
-      if (e) {
-        u = w;
-        nb = e;
+// The vertices farther than delta from this lane's vertex (n x n D in LDS,
+// read down the columns of the symmetric matrix; none for lanes at or beyond n).
+__device__ __forceinline__ uint64_t far_from(const double* D, int n, double delta) {
+  const int lane = threadIdx.x & 63;
+  const int at = lane < n ? lane : 0;
+  uint64_t a = 0;
+#pragma unroll 4
+  for (int v = 0; v < n; ++v)
+    a |= static_cast<uint64_t>(v != lane && D[v * n + at] > delta) << v;
+  return lane < n ? a : 0;
+}
+
+// A vertex cover of at most k vertices of the graph induced on the vertices U
+// (lane u holds u's neighbours in adj), by one wave: true, and the cover in
+// *cover, if there is one. U and k are wave-uniform. Depth first: vertices with
+// more uncovered pairs than the budget join the cover (any cover within the
+// budget holds them), a vertex with one uncovered pair sends its neighbour in,
+// and where no vertex has three, a vertex of a cycle may join; else the vertex
+// v of most uncovered pairs either joins, or all its neighbours do. Every
+// branch spends at least one of the budget and the second at least three, so
+// a budget of k takes fewer than 1.47^k + 1 leaves.
+__device__ bool wave_cover(uint64_t adj, uint64_t U, int k, uint64_t* cover) {
+  const int lane = threadIdx.x & 63;
+  uint64_t C = 0;
+  uint64_t stC = 0;  // lane i: pending branch i (its cover and budget)
+  int stk = 0, sp = 0;
+  for (;;) {
+    bool dead = k < 0;
+    while (!dead) {
+      const uint64_t alive = U & ~C;
+      const unsigned deg =
+          ((alive >> lane) & 1) ? static_cast<unsigned>(__popcll(adj & alive)) : 0u;
+      const uint64_t forced = __ballot(deg > static_cast<unsigned>(k));
+      if (forced) {
+        C |= forced;
+        k -= __popcll(forced);
+        dead = k < 0;
+        continue;
+      }
+      const uint64_t some = __ballot(deg > 0);
+      if (!some) {
+        *cover = C;
+        return true;
+      }
+      if (k == 0) {
+        dead = true;
         break;
       }
+      const uint64_t one = __ballot(deg == 1);
+      if (one) {  // its neighbour covers at least as much as it does
+        const uint64_t nb = lane64(adj, __builtin_ctzll(one)) & alive;
+        C |= nb & (~nb + 1);
+        --k;
+        continue;
+      }
+      const unsigned best =
+          __builtin_amdgcn_readfirstlane(__ockl_wfred_max_u32((deg << 6) | (63u - lane)));
+      const int v = 63 - static_cast<int>(best & 63), dmax = static_cast<int>(best >> 6);
+      if (dmax > 2) {
+        const int pairs = static_cast<int>(
+            __builtin_amdgcn_readfirstlane(__ockl_wfred_add_u32(deg)) / 2);
+        if (pairs > k * dmax) {
+          dead = true;
+          break;
+        }
+        if (dmax <= k && sp < kCoverStack) {  // later: all of v's neighbours
+          const uint64_t nb = lane64(adj, v) & alive;
+          if (lane == sp) {
+            stC = C | nb;
+            stk = k - dmax;
+          }
+          ++sp;
+        }
+      }
+      C |= uint64_t{1} << v;
+      --k;
     }
-    if (u < 0) return true;
-    if (step >= k) return false;
-    const int v = __builtin_ctzll(nb);
-    c |= ((path >> step) & 1) ? (uint64_t{1} << v) : (uint64_t{1} << u);
+    if (sp == 0) return false;
+    --sp;
+    C = lane64(stC, sp);
+    k = __builtin_amdgcn_readlane(stk, sp);
   }
 }
 
-// Whether at most f - |F| of the vertices outside S and F cover every pair
-// among them farther apart than delta (the pairs reaching S or F are settled
-// by the caller). All threads of the workgroup call it with the same
-// arguments and get the same answer. First the vertices with more uncovered
-// pairs than the budget go into the cover, all of them at once and again
-// until none is left (any cover within the budget contains each of them):
-// every wave does this alone, lane u holding vertex u's neighbours, so the
-// waves agree without a barrier. Then, unless no pair is left or more pairs
-// are left than the budget's vertices can touch, the 2^k paths of the search
-// tree are spread over the threads, a round of them at a time, until one
-// covers everything.
-__device__ bool cover_feasible(const double* D, int n, double delta, uint64_t S, uint64_t F, int f,
-                               uint64_t* adj) {
-  const uint64_t U = low_bits(n) & ~S & ~F;
-  int k = f - __popcll(F);
-  if (k < 0 || k > 40) return false;  // f <= 16 under the subset limit of the entry points
-  const int t = threadIdx.x, lane = t & 63;
-  const bool live = lane < n && ((U >> lane) & 1);
-  uint64_t a = 0;
-  if (live) {
-    const double* row = D + lane * n;
-    for (int v = 0; v < n; ++v)
-      a |= static_cast<uint64_t>(v != lane && ((U >> v) & 1) && row[v] > delta) << v;
-  }
-  if (t < 64) adj[t] = a;
-  uint64_t C = 0;
-  for (;;) {
-    const uint64_t forced = __ballot(live && __popcll(a & ~C) > k && !((C >> lane) & 1));
-    if (!forced) break;
-    C |= forced;
-    k -= __popcll(forced);
-    if (k < 0) break;
-  }
-  bool found = false;
-  if (k >= 0) {
-    const bool rest = live && !((C >> lane) & 1);
-    const int deg = rest ? __popcll(a & ~C) : 0;
-    int edges = deg, dmax = deg;
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) {
-      edges += __shfl_xor(edges, m, 64);
-      const int o = __shfl_xor(dmax, m, 64);
-      dmax = o > dmax ? o : dmax;
-    }
-    edges /= 2;
-    if (edges == 0) {
-      found = true;
-    } else if (edges <= k * dmax) {
-      __syncthreads();  // adj written
-      const int64_t paths = int64_t{1} << k;
-      const int64_t rounds = (paths + kCoverThreads - 1) / kCoverThreads;
-      for (int64_t r = 0; r < rounds; ++r) {
-        const int64_t path = r * kCoverThreads + t;
-        const bool mine = path < paths && cover_path(adj, U, C, k, path);
-        if (__syncthreads_or(mine)) {
-          found = true;
-          break;
+// The values of v (count of them, in LDS, with room for the next power of two)
+// sorted in descending order by the whole workgroup (bitonic).
+__device__ void sort_descending(double* v, int count) {
+  int size = 1;
+  while (size < count) size <<= 1;
+  for (int i = count + threadIdx.x; i < size; i += blockDim.x) v[i] = -1.0;  // below any distance
+  __syncthreads();
+  for (int k = 2; k <= size; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int t = threadIdx.x; t < size / 2; t += blockDim.x) {
+        const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
+        const double a = v[i], b = v[i + j];
+        if ((a < b) == ((i & k) == 0)) {
+          v[i] = b;
+          v[i + j] = a;
         }
       }
+      __syncthreads();
     }
+}
+
+// The mask of the first (n - f)-subset of least diameter (n x n D in LDS); all
+// kCoverThreads threads of the workgroup take part.
+__device__ uint64_t cover_search(const double* D, int n, int f) {
+  __shared__ double dv[kNmax * kNmax / 2 + 1];
+  __shared__ int fits[kCoverWaves];
+  __shared__ uint64_t covers[kCoverWaves];
+  const int s = n - f, P = n * (n - 1) / 2;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t all = low_bits(n);
+  // the pair distances in descending order, then 0
+  for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
+    const int i = idx / n, j = idx % n;
+    if (i < j) dv[direct_entry(n, i, j)] = D[idx];
   }
-  __syncthreads();  // adj is rebuilt by the next call
-  return found;
+  __syncthreads();
+  sort_descending(dv, P);
+  if (threadIdx.x == 0) dv[P] = 0.0;
+  __syncthreads();
+  // largest j whose distance dv[j] admits a cover (j = 0 always does: no pair
+  // is farther apart than the largest distance), 16 of them tested at a time
+  int lo = 0, hi = P;
+  while (lo < hi) {
+    const int span = hi - lo;
+    auto at = [&](int w) { return lo + (span * (w + 1) + kCoverWaves - 1) / kCoverWaves; };
+    uint64_t c;
+    const bool ok = wave_cover(far_from(D, n, dv[at(wave)]), all, f, &c);
+    if (lane == 0) fits[wave] = ok;
+    __syncthreads();
+    int most = 0;  // thresholds that fit come first
+    while (most < kCoverWaves && fits[most]) ++most;
+    __syncthreads();
+    const int l = most > 0 ? at(most - 1) : lo;
+    hi = most < kCoverWaves ? at(most) - 1 : hi;
+    lo = l;
+  }
+  const uint64_t adj = far_from(D, n, dv[lo]);
+  uint64_t cover = 0;
+  wave_cover(adj, all, f, &cover);  // every wave finds the same one
+  uint64_t W = uniform64(all & ~cover);  // a set of diameter at most delta, s members or more
+  uint64_t S = 0, F = 0;                 // decided: in, out (of the vertices below pos)
+  for (int pos = 0; pos < n && __popcll(S) < s;) {
+    // this wave's vertex: the wave-th one from pos on that W lacks and S allows
+    uint64_t rest = ~W & ~F & all & ~low_bits(pos);
+    const int tests = __popcll(rest);
+    if (tests == 0) break;
+    uint64_t before = 0;  // those ahead of it
+    for (int t = 0; t < wave && rest; ++t) {
+      before |= rest & (~rest + 1);
+      rest &= rest - 1;
+    }
+    bool ok = false;
+    uint64_t c = 0, S2 = 0, F2 = 0;
+    if (rest) {
+      const int v = __builtin_ctzll(rest);
+      const uint64_t mine = uint64_t{1} << v;
+      const uint64_t Sv = S | (W & low_bits(v) & ~low_bits(pos));
+      const uint64_t far = lane64(adj, v);
+      S2 = Sv | mine;
+      // out: those before it, and whatever is far from a member
+      const uint64_t touched = __ballot(((~S2 >> lane) & 1) && (adj & S2) != 0) & all;
+      F2 = (F | before | touched) & ~S2;
+      if (!(far & Sv) && __popcll(Sv) < s && __popcll(F2) <= f)
+        ok = wave_cover(adj, all & ~S2 & ~F2, f - __popcll(F2), &c);
+    }
+    if (lane == 0) {
+      fits[wave] = ok;
+      covers[wave] = c;
+    }
+    __syncthreads();
+    int first = 0;
+    while (first < kCoverWaves && !fits[first]) ++first;
+    const uint64_t found = first < kCoverWaves ? covers[first] : 0;
+    __syncthreads();
+    // the vertex that joins, or the last one tested, and what precedes it
+    const int through = first < kCoverWaves ? first : (tests < kCoverWaves ? tests : kCoverWaves) - 1;
+    uint64_t left = ~W & ~F & all & ~low_bits(pos), out = 0;
+    for (int t = 0; t < through; ++t) {
+      out |= left & (~left + 1);
+      left &= left - 1;
+    }
+    const int v = __builtin_ctzll(left);
+    S |= W & low_bits(v) & ~low_bits(pos);
+    F |= out;
+    if (first < kCoverWaves) {
+      S |= uint64_t{1} << v;
+      const uint64_t touched = __ballot(((~S >> lane) & 1) && (adj & S) != 0) & all;
+      F = (F | touched) & ~S;
+      W = S | (all & ~S & ~F & ~found);
+    } else {
+      F |= uint64_t{1} << v;
+    }
+    S = uniform64(S);
+    F = uniform64(F);
+    W = uniform64(W);
+    pos = v + 1;
+  }
+  // the s lowest members
+  while (__popcll(W) > s) W &= ~(uint64_t{1} << (63 - __builtin_clzll(W)));
+  return W;
 }
 
 __global__ __launch_bounds__(kCoverThreads) void k_mda_cover(DistSums ds, int f,
                                                              int32_t* __restrict__ sel) {
   __shared__ double D[kNmax * kNmax];
-  __shared__ double dv[kNmax * (kNmax - 1) / 2 + 1];
-  __shared__ uint64_t adj[kNmax];
-  const int n = ds.n, s = n - f, P = n * (n - 1) / 2;
   load_dist(ds, D);
-  // the pair distances in descending order (equal ones by pair index), then 0
-  for (int p = threadIdx.x; p < P; p += blockDim.x) {
-    int i = 0, rem = p;
-    while (rem >= n - 1 - i) {
-      rem -= n - 1 - i;
-      ++i;
-    }
-    const double v = D[i * n + i + 1 + rem];
-    int rank = 0, q = 0;
-    for (int a = 0; a < n; ++a)
-      for (int b = a + 1; b < n; ++b, ++q) {
-        const double w = D[a * n + b];
-        rank += (w > v) | ((w == v) & (q < p));
-      }
-    dv[rank] = v;
-  }
-  if (threadIdx.x == 0) dv[P] = 0.0;
-  __syncthreads();
-  // largest j whose distance dv[j] admits a cover (j = 0 always does: no pair
-  // is farther apart than the largest distance)
-  int lo = 0, hi = P;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (cover_feasible(D, n, dv[mid], 0, 0, f, adj)) lo = mid;
-    else hi = mid - 1;
-  }
-  const double delta = dv[lo];
-  uint64_t S = 0, F = 0;
-  for (int v = 0; v < n; ++v) {
-    const uint64_t rest = low_bits(n) & ~S & ~F;
-    if (__popcll(S) == s) {
-      F |= rest;
-      break;
-    }
-    if (__popcll(F) == f) {
-      S |= rest;
-      break;
-    }
-    const int lane = threadIdx.x & 63;  // every wave forms the same mask
-    const uint64_t far = __ballot(lane < n && lane != v && D[v * n + lane] > delta);
-    const uint64_t bit = uint64_t{1} << v;
-    if (far & S) {
-      F |= bit;
-      continue;
-    }
-    const uint64_t S2 = S | bit, F2 = F | (far & rest & ~bit);
-    if (__popcll(F2) <= f && cover_feasible(D, n, delta, S2, F2, f, adj)) {
-      S = S2;
-      F = F2;
-    } else {
-      F |= bit;
-    }
-  }
-  // S has exactly s members; the clamp only guards the sel writes
-  while (__popcll(S) > s) S &= ~(uint64_t{1} << (63 - __builtin_clzll(S)));
-  if (threadIdx.x < 64) write_selected(S, n, nullptr, sel);
+  const uint64_t chosen = cover_search(D, ds.n, f);
+  if (threadIdx.x < 64) write_selected(chosen, ds.n, nullptr, sel);
+}
+
+// Contraction with MDA through covers: workgroup v searches among its q peers
+// as k_peer_mda does.
+__global__ __launch_bounds__(kCoverThreads) void k_peer_cover(DistSums ds,
+                                                              const int32_t* __restrict__ peers,
+                                                              int q, int f,
+                                                              int32_t* __restrict__ sel) {
+  __shared__ double D[kNmax * kNmax];
+  __shared__ int32_t map[kNmax];
+  const int v = blockIdx.x;
+  gather_peers(ds, peers + static_cast<int64_t>(v) * q, q, D, map);
+  const uint64_t chosen = cover_search(D, q, f);
+  if (threadIdx.x < 64) write_selected(chosen, q, map, sel + static_cast<int64_t>(v) * (q - f));
 }
 
 // Dynamic LDS above 64 KB (n near 64 with large s) is requested from the
@@ -939,6 +1029,13 @@ hipError_t enqueue_peer_mda(const DistSums& ds, int nodes, const int32_t* peers,
                             int32_t* sel, hipStream_t s) {
   const int64_t total = binomial(q, f);
   if (total < 1) return hipErrorInvalidValue;
+  // One workgroup enumerates a node's subsets: 12 us for 120 of them, where the
+  // covers take 16, 31 against 21 for 455, 338 against 25 for 33,649.
+  if (total >= kPeerCoverMin) {
+    launch("peer_cover", k_peer_cover, dim3(nodes), dim3(kCoverThreads), 0, s, ds, peers, q, f,
+           sel);
+    return hipGetLastError();
+  }
   const size_t lds = scan_lds_bytes(q, q - f);
   hipError_t e = allow_lds(reinterpret_cast<const void*>(k_peer_mda), lds);
   if (e != hipSuccess) return e;
@@ -948,7 +1045,12 @@ hipError_t enqueue_peer_mda(const DistSums& ds, int nodes, const int32_t* peers,
 }
 
 namespace {
-int64_t g_mda_cover_min = int64_t{1} << 20;
+constexpr int64_t kCoverAutomatic = int64_t{1} << 20;  // the tuning value that leaves the choice
+// The enumeration spreads over the chip: 24 us with its second launch for 3,876
+// subsets and 17 to 22 for 5,005 and 6,188, where the covers take 23, 19 to 23
+// and 20 to 22; 30 against 24 for 33,649, 49 against 31 for 296,010.
+constexpr int64_t kCoverFrom = int64_t{1} << 13;
+int64_t g_mda_cover_min = kCoverAutomatic;
 }  // namespace
 
 int64_t mda_cover_min() { return __atomic_load_n(&g_mda_cover_min, __ATOMIC_RELAXED); }
@@ -957,8 +1059,8 @@ void set_mda_cover_min(int64_t subsets) {
 }
 
 bool mda_uses_cover(int n, int f) {
-  const int64_t total = binomial(n, f);
-  return total < 0 || total >= mda_cover_min();
+  const int64_t total = binomial(n, f), set = mda_cover_min();
+  return total < 0 || total >= (set == kCoverAutomatic ? kCoverFrom : set);
 }
 
 hipError_t enqueue_mda_select(const DistSums& ds, int f, void* scratch, int32_t* sel,

@@ -210,3 +210,16 @@ def test_shared_mean_leaves_out_what_is_not_finite():
     for r in range(q):
         acc += x[r].astype(np.float64)
     assert np.array_equal(y, np.tile((acc / q).astype(np.float32), (n, 1)))
+
+
+def test_mda_searches_agree():
+    """Nodes of few subsets are enumerated, the others searched through covers:
+    the same first subset of least diameter, ties (small integers) included."""
+    rng = np.random.default_rng(4)
+    for n, q, f in [(11, 10, 3), (14, 11, 4), (22, 22, 2), (22, 23 - 1, 3), (26, 24, 5)]:
+        x = rng.integers(-2, 3, size=(n, 65)).astype(np.float32)
+        peers = np.stack([rng.permutation(n)[:q] for _ in range(n)]).astype(np.int32)
+        got = gf.contract_step("mda", torch.from_numpy(x).to(DEV), torch.from_numpy(peers).to(DEV),
+                               f).cpu().numpy()
+        want, _ = oracle.contract_step("mda", x, peers, f)
+        assert np.array_equal(got, want), (n, q, f)
