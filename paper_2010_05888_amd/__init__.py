@@ -145,14 +145,15 @@ def _check(code: int, where: str):
         raise GarfieldError(code, where, msg)
 
 
-def _stream(x: torch.Tensor) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(x.device).cuda_stream)
+def _stream(x: torch.Tensor) -> int:
+    """The current stream of x's device, as torch holds it (a handle, no object)."""
+    return torch._C._cuda_getCurrentRawStream(x.device.index)
 
 
 def _input(x: torch.Tensor) -> torch.Tensor:
     if not isinstance(x, torch.Tensor) or x.dim() != 2:
         raise ValueError("x must be a 2-D tensor (n vectors of d values)")
-    if x.device.type != "cuda":
+    if not x.is_cuda:
         raise ValueError("x must be on a GPU: this library has no CPU path")
     if x.dtype != torch.float32:
         raise ValueError("x must be float32")
@@ -162,7 +163,7 @@ def _input(x: torch.Tensor) -> torch.Tensor:
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def pairwise_sqdist(x: torch.Tensor) -> torch.Tensor:

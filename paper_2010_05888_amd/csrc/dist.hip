@@ -964,13 +964,19 @@ int g_direct_max_n = 20;
 // Compute units of the current device (256 on MI355X; also the fallback when
 // no device is available, e.g. when only planning on a host without a GPU).
 int device_cus() {
+  static int known[64];  // per device; a device's count does not change
   int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+  if (hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return 256;
+  }
+  if (dev < 64 && (cus = __atomic_load_n(&known[dev], __ATOMIC_RELAXED)) > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       cus <= 0) {
     (void)hipGetLastError();
     return 256;
   }
+  if (dev < 64) __atomic_store_n(&known[dev], cus, __ATOMIC_RELAXED);
   return cus;
 }
 
