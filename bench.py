@@ -191,9 +191,12 @@ def algorithmic(kernel, w):
     the complement mean's own reads."""
     n, f, d = w.n, w.f, w.d
     kernel = kernel[:-4] if kernel.endswith("_seg") else kernel  # segment-table forms
-    if kernel in ("dist_direct", "dist_gram"):
+    if kernel in ("dist_direct", "dist_ring", "dist_gram"):
         return "hbm", 4.0 * n * d, None
-    if kernel == "dist_direct_sum":  # the rows; the design also writes one fp64 sum per coordinate
+    if kernel == "dist_ring_mean" and w.rules[0] != "multikrum_iterated":
+        # the rows, and the mean of the guessed selection: the rule's whole traffic
+        return "hbm", 4.0 * (n + 1) * d, None
+    if kernel in ("dist_direct_sum", "dist_ring_mean"):  # the rows; the design also writes one fp64 sum per coordinate
         return "hbm", 4.0 * n * d, 4.0 * n * d + 8.0 * d
     if kernel == "mean_complement":
         # the rule's mean reads the m selected rows and writes the output; this
@@ -733,7 +736,7 @@ def contract_bench(args):
         agg_bytes = 8.0 * n * d
         rows = {agg: agg_bytes}
         if rule != "median":
-            rows["dist_direct"] = 4.0 * n * d
+            rows["dist_direct"] = rows["dist_ring"] = 4.0 * n * d
         roof = {}
         for kern, nbytes in rows.items():
             if kern in kt:

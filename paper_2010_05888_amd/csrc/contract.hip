@@ -4,11 +4,12 @@
 // One step writes every node's aggregate of its peers to row v of y. The
 // selection kernel (k_peer_select) runs one workgroup per node on the
 // distances of all N rows; the kernels below then aggregate every node in one
-// launch. Mean and Median stage a 256-coordinate tile of all N rows in LDS
-// (each input value read from HBM once, in 1 KB runs) and compute every
-// node's output for that tile from it; Bulyan, bound by its per-node
+// launch. Mean and Median stage a tile of all N rows in LDS (each input value
+// read from HBM once, in runs of 1 KB or more) and compute every node's output
+// for that tile from it, with what the nodes share done once for up to 32 of
+// them (k_mean_shared, k_median_shared); Bulyan, bound by its per-node
 // arithmetic rather than its loads, takes one workgroup per (tile, node), see
-// node_grid. The per-coordinate arithmetic is the single-rule kernels' own.
+// node_grid. The results are the single-rule kernels' own, bit for bit.
 
 #include "aggregate_body.h"
 #include "internal.h"

@@ -14,7 +14,9 @@
 //
 //  * direct (n <= direct_max_n(), default 20): every lane accumulates (x_i - x_j)^2 for all
 //    n(n-1)/2 pairs in fp32 registers over its coordinates. No cancellation,
-//    and identical rows give bit-identical rows of D.
+//    and identical rows give bit-identical rows of D. The register form is
+//    here; long inputs take the ring form (ring_direct.hip), whose tiles are
+//    its workgroups.
 //  * Gram (larger n): G = Y Y^T with Y = X - x_ref (a per-coordinate shift by
 //    one input row, chosen robustly by a small probe), each row of Y rounded
 //    per 256-coordinate stage to 22-bit integers and multiplied exactly on

@@ -1,7 +1,7 @@
-"""MDA's search through vertex covers (Section 3.1 item 3), used from 2^20
-candidate subsets C(n, f) on: the least diameter is the smallest pair distance
-whose graph of farther pairs has a vertex cover of at most f vectors (a binary
-search over the sorted distances, each step a bounded search-tree test), and
+"""MDA's search through vertex covers (Section 3.1 item 3), used where there
+are many candidate subsets C(n, f): the least diameter is the smallest pair
+distance whose graph of farther pairs has a vertex cover of at most f vectors
+(a search over the sorted distances, each step a bounded search-tree test), and
 the winner, the lexicographically first subset of that diameter, is built
 vertex by vertex with the same test.
 
