@@ -66,7 +66,7 @@ def _parse():
                          "each segment (workloads 2-4 and 6)")
     ap.add_argument("--table", action="store_true",
                     help="with --segments: feed the segments as a segment table (vectors stored "
-                         "apart; one launch per 96 segments) instead of one call per segment")
+                         "apart; one launch per 192 segments) instead of one call per segment")
     ap.add_argument("--contract", action="store_true",
                     help="contraction steps instead: 20 nodes of ResNet-18 size, each "
                          "aggregating 17 peers (f = 3), one JSON line per rule")
@@ -434,8 +434,8 @@ def bench_workload(key, args):
         bound, per_launch, design = algorithmic(kern, w)
         if per_launch and args.segments > 1:
             # per-segment calls: one launch per (equal) segment; a segment table: one
-            # launch per 96 segments
-            per_seg = -(-args.segments // 96) if args.table else args.segments
+            # launch per 192 segments
+            per_seg = -(-args.segments // 192) if args.table else args.segments
             per_launch /= per_seg
             design = design / per_seg if design else None
         avg_ms = kt[kern][1] / kt[kern][0]

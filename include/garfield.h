@@ -341,7 +341,7 @@ garfield_status garfield_seg_destroy(garfield_segmented* seg);
  * row-pointer form of every rule: create, accumulate_table, select,
  * aggregate_table).
  *   garfield_seg_accumulate_table(seg, ptrs, dims, K, stream)   adds the
- *       distances of all K segments; one launch per 96 segments, whatever
+ *       distances of all K segments; one launch per 192 segments, whatever
  *       their sizes, instead of one distance step per segment.
  *   garfield_seg_aggregate_table(seg, ptrs, dims, K, outs, stream)   aggregates
  *       every segment with the session's selection; outs (HOST array of K

@@ -483,7 +483,7 @@ class Segmented:
         return out
 
     def accumulate_table(self, table: "SegmentTable"):
-        """Add the distances of every segment of the table (one launch per 96
+        """Add the distances of every segment of the table (one launch per 192
         segments)."""
         if table.n != self.n:
             raise ValueError(f"table has {table.n} vectors, the session {self.n}")

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(kBlock) void k_dist_direct_seg(const float* const* 
   for (int p = 0; p < P; ++p) acc[p] = 0.0f;
   const int b = blockIdx.x;
   const int s = seg_of(tab, b);
-  const int64_t start = static_cast<int64_t>(b - tab.first[s]) * tab.span[s];
+  const int64_t start = (b - tab.first[s]) * tab.span[s];
   const int64_t d = tab.dims[s];
   const int64_t end = start + tab.span[s] < d ? start + tab.span[s] : d;
   direct_accumulate<N, W>(TableRows{ptrs + static_cast<int64_t>(s) * N}, start, end, acc);
@@ -93,9 +93,9 @@ hipError_t for_each_launch(const int64_t* dims, float* const* outs, int K, Per&&
     for (int s = 0; s < tab.count; ++s) {
       const int64_t span = per(dims[g0 + s]);
       tab.first[s] = static_cast<int32_t>(total);
-      tab.span[s] = static_cast<int32_t>(span);
       tab.dims[s] = dims[g0 + s];
-      tab.outs[s] = outs ? outs[g0 + s] : nullptr;
+      if (outs) tab.outs[s] = outs[g0 + s];
+      else tab.span[s] = span;
       total += (dims[g0 + s] + span - 1) / span;
       if (total > 0x7fffffff) return hipErrorInvalidValue;
     }

@@ -2,7 +2,7 @@
 
 Each vector's segments are separate allocations (some one float into their
 buffer, so 4-byte but not 16-byte aligned), with ragged lengths including
-empty and one-float segments, and more segments than one launch takes (96),
+empty and one-float segments, and more segments than one launch takes (192),
 so a batch spans several launches. Checks:
 
 * the selection equals the oracle's on the concatenated vectors whenever
@@ -287,3 +287,24 @@ def test_table_validation():
                                                 1, None, None) == gf.EINVAL
     finally:
         seg.close()
+
+
+@pytest.mark.parametrize("n,f", [(7, 1), (21, 4)])  # direct and Gram distances
+@pytest.mark.parametrize("K", [192, 193, 385])
+def test_segments_at_the_edges_of_a_launch(n, f, K):
+    """A launch takes 192 segments: exactly one, one more, and two and one more."""
+    g = torch.Generator(device=DEV).manual_seed(K + n)
+    lens = [1 + (37 * k) % 301 for k in range(K)]
+    x = torch.randn((n, sum(lens)), device=DEV, generator=g)
+    x[n - f:] *= 5.0
+    table = gf.SegmentTable([list(torch.split(row, lens)) for row in x])
+    seg = gf.Segmented("multikrum", n, f)
+    seg.accumulate_table(table)
+    sel = seg.select()
+    assert sel.tolist() == list(range(n - f))
+    got = torch.cat(seg.aggregate_table(table))
+    acc = torch.zeros(x.shape[1], dtype=torch.float64, device=DEV)
+    for r in range(n - f):
+        acc += x[r].double()
+    assert torch.equal(got, (acc / (n - f)).float())
+    seg.close()
