@@ -485,8 +485,11 @@ hipError_t enqueue_mean_nodes(const float* x, int n, int64_t d, int nodes, const
   // form's grows with n: 1.1 to 1.3 times as fast with k near n (n = 9 to 32,
   // d = 10^6 and 8 * 10^6), 0.83 with k = 1 of n = 32, 0.96 to 1.03 with k = 1 of
   // n = 24. Short rows would leave its larger tiles too few workgroups (d = 10^5:
-  // 0.8 to 1.04).
-  if (ascending && n <= kSharedMaxRows && 4 * k + 16 >= n && d >= kSharedMinCoords)
+  // 0.8 to 1.04). Below 2^20 coordinates few rows per node don't pay either: a
+  // Multi-Krum step with k = 3 of n = 14 at d = 3 * 10^5 takes 26.0 us in the form
+  // below and 28.9 us in this one, k = 14 of n = 20 at 2.7 * 10^5 42.9 and 41.4 us.
+  const bool rows_pay = d >= int64_t{1} << 20 ? 4 * k + 16 >= n : 3 * k >= 2 * n;
+  if (ascending && n <= kSharedMaxRows && rows_pay && d >= kSharedMinCoords)
     return mean_shared_dispatch<1>(x, n, d, nodes, rows, k, y, s);
   launch("mean_nodes", k_mean_nodes, dim3(tile_grid(d)), dim3(kBlock),
          static_cast<uint32_t>(tile_bytes(n, nodes * k)), s, x, n, d, nodes, rows, k, y);
