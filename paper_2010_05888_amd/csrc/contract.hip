@@ -183,8 +183,10 @@ __global__ __launch_bounds__(kBlock) void k_median_nodes(const float* __restrict
 // on this chip (4.6).
 //
 // A node whose list repeats a row (its mask has fewer rows) takes its listed
-// rows in order, and so does the mean of a wave that holds an infinity or NaN
-// (a weight of 0 would not leave those out).
+// rows in order, and so do all nodes of a wave that holds what the shared work
+// would carry over from rows a node does not hear: for the mean an infinity or
+// NaN (a weight of 0 would not leave those out), for the median a NaN (the
+// networks' minima and maxima drop it, and another value stands there twice).
 constexpr int kSharedMaxRows = 32;
 constexpr int kSharedCoords = 2 * kBlock;
 constexpr int kSharedMaxAbsent = 6;
@@ -344,11 +346,15 @@ __global__ __launch_bounds__(kBlock) void k_median_shared(const float* __restric
     s0[i] = t.x;
     s1[i] = t.y;
   }
+  bool nan = false;
+#pragma unroll
+  for (int i = 0; i < N; ++i) nan |= __builtin_isunordered(s0[i], s1[i]);
+  const bool ordered = __ballot(nan) == 0;
   SortNet<N>::run(s0);
   SortNet<N>::run(s1);
   for (int v = 0; v < nodes; ++v) {
     float o0, o1;
-    if (__builtin_amdgcn_readfirstlane(whole[v])) {
+    if (ordered && __builtin_amdgcn_readfirstlane(whole[v])) {  // uniform
       float e0[X > 0 ? X : 1], e1[X > 0 ? X : 1];
 #pragma unroll
       for (int k = 0; k < X; ++k) {

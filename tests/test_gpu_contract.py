@@ -212,6 +212,23 @@ def test_shared_mean_leaves_out_what_is_not_finite():
     assert np.array_equal(y, np.tile((acc / q).astype(np.float32), (n, 1)))
 
 
+@pytest.mark.parametrize("n,absent", [(5, 1), (9, 2), (12, 3), (20, 3), (20, 6)])
+def test_shared_median_leaves_out_what_is_nan(n, absent):
+    """NaN and infinities in rows that a node does not hear leave its median as
+    it is, for odd and even counts of rows and whole and ragged tiles."""
+    q, d = n - absent, (1 << 18) + 3
+    rng, x = _inputs(n, d, 31 * n + absent)
+    at = rng.random(d)
+    x[n - 1, at < 0.5] = np.nan  # nobody hears the last rows
+    x[n - absent, at > 0.7] = -np.inf
+    peers = np.stack([rng.permutation(q) for _ in range(n)]).astype(np.int32)
+    got = gf.contract_step("median", torch.from_numpy(x).to(DEV), torch.from_numpy(peers).to(DEV),
+                           0).cpu().numpy()
+    srt = np.sort(x[:q].astype(np.float64), axis=0)
+    want = ((srt[(q - 1) // 2] + srt[q // 2]) / 2).astype(np.float32)
+    assert np.array_equal(got, np.tile(want, (n, 1)))
+
+
 def test_mda_searches_agree():
     """Nodes of few subsets are enumerated, the others searched through covers:
     the same first subset of least diameter, ties (small integers) included."""
