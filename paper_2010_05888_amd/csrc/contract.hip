@@ -280,6 +280,14 @@ __global__ __launch_bounds__(kBlock) void k_mean_shared(const float* __restrict_
   }
 }
 
+// e <= at in the order the networks sort by (their minimum takes -0 before +0,
+// where a comparison of floats calls the two equal): the order of the bits, whose
+// magnitudes count downwards where at is negative.
+__device__ __forceinline__ bool sorts_to(float e, float at) {
+  const int32_t b = __float_as_int(at), flip = (b >> 31) & 0x7fffffff;
+  return (__float_as_int(e) ^ flip) <= (b ^ flip);
+}
+
 // The rank-T value of the N sorted values s (rank r at s[Net::reg(r)]) without
 // the X values e (ascending).
 template <int N, int X, int T>
@@ -289,7 +297,7 @@ __device__ __forceinline__ float rank_without(const float* s, const float* e) {
 #pragma unroll
   for (int k = X - 1; k >= 0; --k) {
     const float at = s[Net::reg(T + k)];
-    r = e[k] <= at ? r : at;
+    r = sorts_to(e[k], at) ? r : at;
   }
   return r;
 }

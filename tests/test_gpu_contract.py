@@ -229,6 +229,27 @@ def test_shared_median_leaves_out_what_is_nan(n, absent):
     assert np.array_equal(got, np.tile(want, (n, 1)))
 
 
+@pytest.mark.parametrize("n,absent", [(4, 1), (9, 2), (12, 3), (20, 3), (19, 6), (8, 0)])
+def test_medians_keep_the_sign_of_a_zero(n, absent):
+    """Rows with zeros of both signs, -0 before +0: the same bits from the form
+    that shares a coordinate's rows and, on the first coordinates alone, from
+    each node's own network."""
+    q, d = n - absent, (1 << 18) + 5
+    rng = np.random.default_rng(n)
+    x = rng.choice(np.array([-1.5, -0.0, 0.0, 0.0, 2.0], np.float32), (n, d))
+    peers = np.stack([rng.permutation(n)[:q] for _ in range(n)]).astype(np.int32)
+    pt = torch.from_numpy(peers).to(DEV)
+    got = gf.contract_step("median", torch.from_numpy(x).to(DEV), pt, 0).cpu().numpy()
+    own = gf.contract_step("median", torch.from_numpy(x[:, :4099].copy()).to(DEV), pt, 0)
+    bits = x.view(np.int32)
+    keys = np.sort((bits ^ ((bits >> 31) & 0x7fffffff))[peers], axis=1)
+    srt = (keys ^ ((keys >> 31) & 0x7fffffff)).view(np.float32).astype(np.float64)
+    lo, hi = srt[:, (q - 1) // 2], srt[:, q // 2]
+    want = (lo if q % 2 else (lo + hi) * 0.5).astype(np.float32).view(np.int32)
+    assert np.array_equal(got.view(np.int32), want)
+    assert np.array_equal(own.cpu().numpy().view(np.int32), want[:, :4099])
+
+
 def test_mda_searches_agree():
     """Nodes of few subsets are enumerated, the others searched through covers:
     the same first subset of least diameter, ties (small integers) included."""
