@@ -825,10 +825,13 @@ __device__ uint64_t cover_search(const double* D, int n, int f) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t all = low_bits(n);
-  // the pair distances in descending order, then 0
+  // the pair distances in descending order, then 0; a NaN, which the
+  // comparisons of the sort would scatter, as the 0 it counts for in the tests
+  // (it is farther than nothing, as in the enumeration's diameters)
   for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
     const int i = idx / n, j = idx % n;
-    if (i < j) dv[direct_entry(n, i, j)] = D[idx];
+    const double v = D[idx];
+    if (i < j) dv[direct_entry(n, i, j)] = v > 0.0 ? v : 0.0;
   }
   __syncthreads();
   sort_descending(dv, P);

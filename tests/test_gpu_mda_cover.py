@@ -114,6 +114,33 @@ def test_cover_equals_enumeration(n, f, d):
     assert torch.equal(oa, ob)
 
 
+@pytest.mark.parametrize("n,f,bad", [(18, 5, [3]), (20, 5, [0, 11]), (20, 8, [7, 8, 19])])
+def test_rows_that_are_not_finite(n, f, bad):
+    # NaN distances are farther than nothing in both searches, infinite ones
+    # than everything else; the direct engine (n <= 20) keeps both as they are
+    g = torch.Generator(device=DEV).manual_seed(n + f)
+    xt = torch.randn((n, 3001), device=DEV, generator=g)
+    for value in (float("nan"), float("inf")):
+        xt[bad, 17] = value
+        (oa, sa), (ob, sb) = _both(xt, f)
+        assert torch.equal(sa, sb), (value, sa.tolist(), sb.tolist())
+        assert torch.equal(oa.view(torch.int32), ob.view(torch.int32))
+    # a contraction's nodes, enumerated by the plain rule
+    xt[bad, 17] = float("nan")
+    q, fq = n - 2, f - 2
+    rng = np.random.default_rng(n)
+    peers = np.stack([np.sort(rng.permutation(n)[:q]) for _ in range(n)]).astype(np.int32)
+    y = gf.contract_step("mda", xt, torch.from_numpy(peers).to(DEV), fq)
+    old = gf.set_mda_cover_min(ENUMERATE)
+    try:
+        for v in range(n):
+            want, _ = gf.mda(xt[torch.from_numpy(peers[v]).to(DEV).long()].contiguous(), fq)
+            same = (y[v] == want) | (y[v].isnan() & want.isnan())
+            assert bool(same.all()), v
+    finally:
+        gf.set_mda_cover_min(old)
+
+
 def test_fig3_shape_n39():
     # the micro-benchmark's n = 39, f = 9 (211 million subsets) at d = 10^7
     g = torch.Generator(device=DEV).manual_seed(39)
