@@ -1070,7 +1070,7 @@ DistPlan plan_distances(int n, int64_t d, const float* x, DirectForm form) {
     p.engine = kEngineDirect;
     p.entries = n * (n - 1) / 2;
     p.width = load_width(x);
-    if (p.width == 4 && (form == kFormRing || (form == kFormAuto && ring_pays(n, d)))) {
+    if (p.width == 4 && form == kFormAuto && ring_pays(n, d)) {
       p.ring = true;
       p.chunk = ring_stage(n);
       p.tiles = device_cus();

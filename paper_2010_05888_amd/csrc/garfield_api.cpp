@@ -146,12 +146,12 @@ MeanPlan plan_mean(const float* x, int n, int f, int64_t d, int m, const float* 
   const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), o0 = reinterpret_cast<uintptr_t>(out);
   const uintptr_t row = static_cast<uintptr_t>(d) * sizeof(float);
   const bool apart = o0 + row <= x0 || o0 >= x0 + static_cast<uintptr_t>(n) * row;
-  const bool want = guessable && apart && guess_pays(n, d, f, m, out);
-  p.dist = plan_distances(n, d, x, want ? kFormRing : kFormAuto);
-  p.guess = want && p.dist.ring;
+  p.dist = plan_distances(n, d, x);
+  p.guess = guessable && apart && p.dist.ring && guess_pays(n, d, f, m, out);
   p.colsum = out && use_colsum(p.dist, m);
-  // reserved whether or not the rule is guessable: the rules' sizes agree
-  p.guess_bytes = guess_pays(n, d, f, m, out) ? align256(kGuessRuns * sizeof(uint64_t)) : 0;
+  // reserved wherever a guess fits the distance step, made or not: the rules
+  // that average m rows of n x d need the same space
+  p.guess_bytes = p.dist.ring && n <= kGuessMaxN ? align256(kGuessRuns * sizeof(uint64_t)) : 0;
   p.colsum_bytes = p.colsum ? align256(static_cast<size_t>(d) * sizeof(double)) : 0;
   return p;
 }
@@ -692,8 +692,9 @@ garfield_status garfield_seg_destroy(garfield_segmented* seg) {
 
 size_t garfield_workspace_bytes(int rule, int n, int f, int64_t d, int m) {
   if (n < 1 || n > GARFIELD_NMAX || f < 0 || d < 0) return 0;
-  // Plan for float-aligned rows and outputs: the same plan as every call of
-  // the rule with these sizes.
+  // Plan for float-aligned rows and an output apart from them: what a call of
+  // the rule with these sizes takes, and no less than one without an output or
+  // with one inside x takes.
   const float* x = reinterpret_cast<const float*>(uintptr_t{4});
   const float* out = x + static_cast<int64_t>(n) * d;
   switch (rule) {

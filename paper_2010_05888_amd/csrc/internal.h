@@ -35,9 +35,12 @@ struct DistPlan {
 int direct_max_n();
 void set_direct_max_n(int n);
 
-// How the direct engine streams long inputs: in its register form always, in
-// its ring form where that is faster (ring_pays), or always in its ring form.
-enum DirectForm { kFormRegisters, kFormAuto, kFormRing };
+// How the direct engine streams long inputs: in its ring form where that is
+// faster (ring_pays), or in its register form always. The two group the fp32
+// sums differently, so every call on an n x d matrix takes the form that n and
+// d alone decide, whatever else it does: the distances, and with them the
+// selection, are the same bits from each.
+enum DirectForm { kFormAuto, kFormRegisters };
 DistPlan plan_distances(int n, int64_t d, const float* x, DirectForm form = kFormAuto);
 
 // Compute units of the current device (256 on MI355X; also the fallback when

@@ -506,16 +506,17 @@ int ring_stage(int n) { return stage_of<2>(n); }
 
 // The ring form has a longer start and end than the register form (one
 // workgroup per CU: the first loads' latency, then one reduction over all
-// pairs, with nothing beside them), and streams faster in between. Measured on
-// N(0, 1) rows, ring against register form: n = 7 40.5 against 38.2 us at 9 M
-// coordinates and 107 against 114 at 25.6 M; n = 11 43.4 against 42.2 us at
-// 6 M, 62.3 against 63.5 at 9 M, 170 against 190 at 25.6 M; n = 16 26.3
-// against 27.9 us at 2 M and 93.8 against 107 at 9 M; n = 20 29.1 against 25.1
-// us at 1.5 M, 35.4 against 37.4 at 2 M, 137 against 147 at 9 M.
+// pairs, with nothing beside them), and streams faster in between. Whole calls
+// of garfield_pairwise_sqdist on N(0, 1) rows, ring against register form: n = 2
+// 16.7 against 16.9 us at 8.4 M coordinates and 26.1 against 28.1 at 16.8 M;
+// n = 5 32.5 against 33.0 and 57.5 against 60.7; n = 7 42.7 against 45.2 and
+// 77.1 against 84.1; n = 12 67.4 against 77.6 and 128 against 150; n = 11's pass
+// alone at 6 M 43.4 against 42.2. n = 16 31.2 against 32.8 us at 2.1 M and 89.5
+// against 114 at 8.4 M; n = 20 38.8 against 41.9 and 124 against 143, its pass
+// alone at 1.5 M 29.1 against 25.1.
 bool ring_pays(int n, int64_t d) {
   if (n < 2 || n > kDirectMaxNLimit || d > int64_t{1} << 38) return false;
-  const int shift = n >= 16 ? 21 : (n >= 9 ? 23 : 24);
-  return d >= int64_t{1} << shift;
+  return d >= int64_t{1} << (n >= 16 ? 21 : 23);
 }
 
 // A guess costs its launch and the look at it afterwards (4 to 10 us) and

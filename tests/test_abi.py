@@ -151,6 +151,21 @@ def test_workspace_bytes(lib):
     assert gf.workspace_bytes("mda", 64, 31, 10) == 0
 
 
+@pytest.mark.parametrize("d", [1 << 21, (1 << 23) - 1, 1 << 23, 10 ** 7, 1 << 24, 25_557_032])
+def test_a_rule_reports_the_scratch_of_its_distances(lib, d):
+    # a call that makes the selection alone takes the distance step's scratch,
+    # and one form of that step serves every call on n x d values
+    for n in (2, 3, 5, 7, 8, 9, 15, 16, 20, 21):
+        dist = gf.workspace_bytes("dist", n, 0, d)
+        f = max(0, (n - 3) // 2)
+        assert gf.workspace_bytes("mda", n, f, d) >= dist
+        if n >= 2 * f + 3:
+            for m in {1, 2, n - f}:
+                assert gf.workspace_bytes("multikrum", n, f, d, m) >= dist
+                assert gf.workspace_bytes("multikrum", n, f, d, m) == \
+                    gf.workspace_bytes("multikrum_iterated", n, f, d, m)
+
+
 def test_engine_selection(lib):
     old = gf.set_direct_max_n(20)
     try:

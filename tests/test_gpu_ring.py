@@ -14,7 +14,7 @@ DEV = "cuda:0"
 
 
 def _least(n):
-    return 1 << (21 if n >= 16 else 23 if n >= 9 else 24)
+    return 1 << (21 if n >= 16 else 23)
 
 
 def _rows(n, d, seed):
@@ -131,6 +131,40 @@ def test_column_sums_without_a_guess():
     (out, sel), names = _kernels(lambda: gf.multikrum_iterated(x, f, m))
     assert {"dist_ring_mean", "mean_complement"} <= names and "guess" not in names
     assert torch.equal(out, _mean64(x, sel.tolist()))
+
+
+@pytest.mark.parametrize("n,f,d", [(5, 1, (1 << 23) + 1), (7, 1, (1 << 23) + 1),
+                                   (8, 1, (1 << 24) - 3), (16, 2, (1 << 21) + 3)])
+def test_every_call_sees_the_same_distances(n, f, d):
+    """Two outliers, one the other's mirror image among rows that are their own:
+    their scores are equal but for the order of the sums, so the rounding of the
+    distances decides which one is left out, and every call decides alike."""
+    for seed in range(6):
+        half = _rows(n, (d + 1) // 2, 100 * n + seed)
+        x = torch.cat([half, half[:, :d // 2].flip(1)], 1)
+        x[n - 2] = 3.0 * _rows(1, d, 7 * n + seed)[0]
+        x[n - 1] = x[n - 2].flip(0)
+        m = n - f
+        _, sel = gf.multikrum(x, f, m)
+        assert torch.equal(gf.multikrum(x, f, m, aggregate=False)[1], sel)
+        out, fixed = torch.empty(d, device=DEV), torch.empty_like(sel)
+        s = torch.cuda.current_stream().cuda_stream
+        assert gf.load().garfield_multikrum_noalloc(
+            x.data_ptr(), n, f, d, m, out.data_ptr(), fixed.data_ptr(), s) == gf.OK
+        assert torch.equal(fixed, sel)
+        if f > 1:
+            continue
+        # the scores, as garfield_pairwise_sqdist's distances give them (the k
+        # smallest of a row added as a balanced tree)
+        D = gf.pairwise_sqdist(x).tolist()
+        scores = []
+        for i in range(n):
+            s = sorted(D[i][j] for j in range(n) if j != i)[:n - f - 2]
+            s += [0.0] * (16 - len(s))
+            while len(s) > 1:
+                s = [a + b for a, b in zip(s[::2], s[1::2])]
+            scores.append((s[0], i))
+        assert sel.tolist() == sorted(i for _, i in sorted(scores)[:m])
 
 
 def test_out_inside_the_input_is_not_guessed():
