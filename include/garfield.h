@@ -293,9 +293,10 @@ double garfield_variance_margin(int rule, int n, int f, const double* stats_host
  * in). A segmented aggregation accumulates the segments' distance matrices,
  * makes the rule's one selection from the total, then aggregates every
  * segment with that selection: the result equals the rule applied to the
- * concatenated vectors (the selection up to the rounding of the fp64 sums,
- * the aggregate of each segment exactly as the unsegmented call computes
- * those coordinates).
+ * concatenated vectors (the selection up to the rounding of the distances,
+ * whose fp32 runs of at most 16 squares fall on other coordinates and whose
+ * fp64 sums are added in another order; the aggregate of each segment exactly
+ * as the unsegmented call computes those coordinates).
  *
  *   garfield_seg_create(rule, n, f, m, &seg)   rule: GARFIELD_RULE_KRUM,
  *       _MULTIKRUM or _MULTIKRUM_ITERATED (m as for garfield_multikrum),
@@ -348,11 +349,14 @@ garfield_status garfield_seg_destroy(garfield_segmented* seg);
  *       DEVICE pointers, each to dims[s] fp32 values, 4-byte aligned).
  * Distances: the direct engine for n <= 20, else the Gram engine over the
  * table (one reference row, probed on the longest segment, for every
- * segment). Results equal those of garfield_seg_accumulate /
- * garfield_seg_aggregate on the same segments held as n x d matrices for
- * n <= 20 (whatever the engine threshold); for n > 20 the distances differ
- * from the matrix sessions' only by rounding (the Gram engine's bound). A
- * launch takes at most 2^31 - 1 workgroups or stages (GARFIELD_ETOOBIG).
+ * segment). For n <= 20 the distances of a segment are formed as
+ * garfield_seg_accumulate forms those of the same segment held as an n x d
+ * matrix (at the default engine threshold, which tables do not read), whatever
+ * its length: one segment gives the same bits, and several differ by the order
+ * in which their fp64 sums are added. For n > 20 they differ from the matrix
+ * sessions' only by rounding (the Gram engine's bound). The same selection
+ * gives the same bits in every output. A launch takes at most 2^31 - 1
+ * workgroups or stages (GARFIELD_ETOOBIG).
  */
 garfield_status garfield_seg_accumulate_table(garfield_segmented* seg, const float* const* ptrs,
                                               const int64_t* dims, int K, void* stream);

@@ -107,8 +107,9 @@ garfield_status run_distances_on(const DistPlan& plan, void* base, const float* 
 }
 
 garfield_status run_distances(const float* x, int n, int64_t d, size_t extra, DistSums* ds,
-                              void** extra_ptr, hipStream_t s, int fold_entries = 0) {
-  const DistPlan plan = plan_distances(n, d, x);
+                              void** extra_ptr, hipStream_t s, int fold_entries = 0,
+                              DirectForm form = kFormAuto) {
+  const DistPlan plan = plan_distances(n, d, x, form);
   const size_t dist_bytes = dist_workspace_bytes(plan);
   void* base = nullptr;
   garfield_status st = workspace(dist_bytes + align256(extra), &base);
@@ -551,7 +552,9 @@ garfield_status garfield_seg_accumulate(garfield_segmented* seg, const float* x,
   if (seg->k == 0) return GARFIELD_OK;  // Median and Average use no distances
   hipStream_t s = static_cast<hipStream_t>(stream);
   DistSums ds;
-  st = run_distances(x, seg->n, d, 0, &ds, nullptr, s);
+  // the register form at any length: the one a segment table takes, whose
+  // distances a matrix session's equal
+  st = run_distances(x, seg->n, d, 0, &ds, nullptr, s, 0, kFormRegisters);
   if (st != GARFIELD_OK) return st;
   return to_status(enqueue_accumulate_dist(ds, seg->dacc, s));
 }

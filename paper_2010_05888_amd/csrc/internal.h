@@ -39,7 +39,8 @@ void set_direct_max_n(int n);
 // faster (ring_pays), or in its register form always. The two group the fp32
 // sums differently, so every call on an n x d matrix takes the form that n and
 // d alone decide, whatever else it does: the distances, and with them the
-// selection, are the same bits from each.
+// selection, are the same bits from each. The segments of a session take the
+// register form, held as matrices or in a table.
 enum DirectForm { kFormAuto, kFormRegisters };
 DistPlan plan_distances(int n, int64_t d, const float* x, DirectForm form = kFormAuto);
 

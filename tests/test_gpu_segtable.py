@@ -289,6 +289,28 @@ def test_table_validation():
         seg.close()
 
 
+@pytest.mark.parametrize("n,f,d", [(7, 1, (1 << 23) + 1), (12, 1, (1 << 23) + 1),
+                                   (17, 1, (1 << 21) + 3), (20, 1, (1 << 21) + 3)])
+def test_a_long_segment_in_a_table_and_in_a_matrix(n, f, d):
+    """Two outliers, one the other's mirror image among rows that are their own:
+    the rounding of the distances decides which one is left out, and a table
+    decides as a matrix session does, however long the segment."""
+    for seed in range(6):
+        g = torch.Generator(device=DEV).manual_seed(10 * n + seed)
+        half = torch.randn((n, (d + 1) // 2), device=DEV, generator=g)
+        x = torch.cat([half, half[:, :d // 2].flip(1)], 1)
+        x[n - 2] = 3.0 * torch.randn(d, device=DEV, generator=g)
+        x[n - 1] = x[n - 2].flip(0)
+        table = gf.SegmentTable([[row] for row in x])
+        got = []
+        for feed in ("accumulate_table", "accumulate"):
+            seg = gf.Segmented("multikrum", n, f)
+            getattr(seg, feed)(table if feed == "accumulate_table" else x)
+            got.append(seg.select().tolist())
+            seg.close()
+        assert got[0] == got[1]
+
+
 @pytest.mark.parametrize("n,f", [(7, 1), (21, 4)])  # direct and Gram distances
 @pytest.mark.parametrize("K", [192, 193, 385])
 def test_segments_at_the_edges_of_a_launch(n, f, K):
