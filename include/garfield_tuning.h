@@ -39,14 +39,17 @@ int garfield_tuning_set_direct_max_n(int n);
 int garfield_tuning_set_fused(int on);
 
 /*
- * MDA's search: from this many candidate subsets C(n, f) on (the default, 2^20,
- * leaves the line to the library, which draws it at 2^13), the least diameter and the lexicographically first subset attaining it are
- * found through vertex covers of the graph of pairs farther apart than a
- * threshold (one workgroup; work grows with 2^f, not with C(n, f)); below it
- * every subset is enumerated. Both give the same subset. Returns the previous
- * value; a negative argument changes nothing. Process-wide; not synchronised
- * with calls in flight.
+ * MDA's search: from this many candidate subsets C(n, f) on, the least
+ * diameter and the lexicographically first subset attaining it are found
+ * through vertex covers of the graph of pairs farther apart than a threshold
+ * (one workgroup; work grows with f, not with C(n, f)); below it every subset
+ * is enumerated. The default, GARFIELD_MDA_COVER_AUTOMATIC (not a count),
+ * leaves the choice to the library, which searches by covers from 2^13 subsets
+ * on. Both give the same subset. Returns the previous value; any other negative
+ * argument changes nothing. Process-wide; not synchronised with calls in
+ * flight.
  */
+#define GARFIELD_MDA_COVER_AUTOMATIC (-9223372036854775807LL - 1)
 long long garfield_tuning_set_mda_cover_min(long long subsets);
 
 /*

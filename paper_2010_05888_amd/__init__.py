@@ -550,9 +550,14 @@ def set_stream_residency(wgs_per_cu: int) -> int:
     return int(load().garfield_tuning_set_stream_residency(wgs_per_cu))
 
 
+MDA_COVER_AUTOMATIC = -(1 << 63)
+
+
 def set_mda_cover_min(subsets: int) -> int:
     """MDA searches by vertex covers from this many subsets C(n, f) on, by
-    enumeration below; returns the previous threshold."""
+    enumeration below; MDA_COVER_AUTOMATIC (the default) leaves the choice to
+    the library. Returns the previous threshold (any other negative argument
+    changes nothing)."""
     return int(load().garfield_tuning_set_mda_cover_min(subsets))
 
 

@@ -247,6 +247,7 @@ garfield_status static_scratch(void** out) {
 
 static_assert(GARFIELD_NMAX == kNmax, "kernel limit and public limit differ");
 static_assert(GARFIELD_DIRECT_MAX_N_LIMIT == kDirectMaxNLimit, "direct engine limit differs");
+static_assert(GARFIELD_MDA_COVER_AUTOMATIC == kMdaCoverAutomatic, "automatic line differs");
 
 }  // namespace
 }  // namespace garfield
@@ -753,7 +754,7 @@ int garfield_tuning_set_direct_max_n(int n) {
 
 long long garfield_tuning_set_mda_cover_min(long long subsets) {
   const long long old = mda_cover_min();
-  if (subsets >= 0) set_mda_cover_min(subsets);
+  if (subsets >= 0 || subsets == GARFIELD_MDA_COVER_AUTOMATIC) set_mda_cover_min(subsets);
   return old;
 }
 

@@ -209,9 +209,11 @@ int64_t sqnorm_parts(int64_t d, const float* grad);
 hipError_t enqueue_variance_stats(const DistSums& ds, int h, const float* grad, int64_t d,
                                   double* partial, double* stats, hipStream_t s);
 
-// MDA subset search: C(n, f) at or above mda_cover_min() subsets (2^13 at its
-// default) by vertex covers of the "farther than" graphs (one workgroup, no scratch), below it
-// by enumeration (scratch: mda_blocks(n, f) x 16 bytes).
+// MDA subset search: C(n, f) at or above mda_cover_min() subsets (at its
+// default, kMdaCoverAutomatic: where that is faster) by vertex covers of the
+// "farther than" graphs (one workgroup, no scratch), below it by enumeration
+// (scratch: mda_blocks(n, f) x 16 bytes).
+constexpr int64_t kMdaCoverAutomatic = INT64_MIN;
 int64_t mda_cover_min();
 void set_mda_cover_min(int64_t subsets);
 bool mda_uses_cover(int n, int f);

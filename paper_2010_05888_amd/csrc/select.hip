@@ -1048,12 +1048,11 @@ hipError_t enqueue_peer_mda(const DistSums& ds, int nodes, const int32_t* peers,
 }
 
 namespace {
-constexpr int64_t kCoverAutomatic = int64_t{1} << 20;  // the tuning value that leaves the choice
 // The enumeration spreads over the chip: 24 us with its second launch for 3,876
 // subsets and 17 to 22 for 5,005 and 6,188, where the covers take 23, 19 to 23
 // and 20 to 22; 30 against 24 for 33,649, 49 against 31 for 296,010.
 constexpr int64_t kCoverFrom = int64_t{1} << 13;
-int64_t g_mda_cover_min = kCoverAutomatic;
+int64_t g_mda_cover_min = kMdaCoverAutomatic;
 }  // namespace
 
 int64_t mda_cover_min() { return __atomic_load_n(&g_mda_cover_min, __ATOMIC_RELAXED); }
@@ -1063,7 +1062,7 @@ void set_mda_cover_min(int64_t subsets) {
 
 bool mda_uses_cover(int n, int f) {
   const int64_t total = binomial(n, f), set = mda_cover_min();
-  return total < 0 || total >= (set == kCoverAutomatic ? kCoverFrom : set);
+  return total < 0 || total >= (set == kMdaCoverAutomatic ? kCoverFrom : set);
 }
 
 hipError_t enqueue_mda_select(const DistSums& ds, int f, void* scratch, int32_t* sel,

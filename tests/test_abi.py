@@ -240,8 +240,29 @@ def test_variance_margin_on_the_host(lib):
 
 def test_tuning_switches_on_the_host(lib):
     # host-side settings only: no device is touched
-    assert lib.garfield_tuning_set_mda_cover_min(-1) == 1 << 20  # the default, unchanged
-    assert lib.garfield_tuning_set_mda_cover_min(5) == 1 << 20
+    automatic = gf.MDA_COVER_AUTOMATIC
+    assert lib.garfield_tuning_set_mda_cover_min(-1) == automatic  # the default, unchanged
+    assert lib.garfield_tuning_set_mda_cover_min(5) == automatic
     assert lib.garfield_tuning_set_mda_cover_min(1 << 20) == 5
+    assert lib.garfield_tuning_set_mda_cover_min(automatic) == 1 << 20
+    assert lib.garfield_tuning_set_mda_cover_min(-1) == automatic
     assert lib.garfield_tuning_set_fused(0) == 1
     assert lib.garfield_tuning_set_fused(1) == 0
+
+
+def test_every_threshold_of_the_cover_search_is_obeyed(lib):
+    # the enumeration keeps 16 bytes of scratch for each of its workgroups, the
+    # search through covers none; C(24, 5) = 42,504 takes covers by default
+    def bytes_at(line):
+        gf.set_mda_cover_min(line)
+        return gf.workspace_bytes("mda", 24, 5, 1000)
+
+    automatic = gf.set_mda_cover_min(-1)
+    try:
+        covers = bytes_at(0)
+        assert bytes_at(automatic) == covers
+        assert bytes_at(42_504) == covers
+        for line in (42_505, 1 << 20, (1 << 20) + 1, 1 << 62):
+            assert bytes_at(line) > covers, line
+    finally:
+        gf.set_mda_cover_min(automatic)
