@@ -45,9 +45,9 @@ int garfield_tuning_set_fused(int on);
  * (one workgroup; work grows with f, not with C(n, f)); below it every subset
  * is enumerated. The default, GARFIELD_MDA_COVER_AUTOMATIC (not a count),
  * leaves the choice to the library, which searches by covers from 2^13 subsets
- * on. Both give the same subset. Returns the previous value; any other negative
- * argument changes nothing. Process-wide; not synchronised with calls in
- * flight.
+ * on where n >= 21 or n >= 2f + 7. Both give the same subset. Returns the
+ * previous value; any other negative argument changes nothing. Process-wide;
+ * not synchronised with calls in flight.
  */
 #define GARFIELD_MDA_COVER_AUTOMATIC (-9223372036854775807LL - 1)
 long long garfield_tuning_set_mda_cover_min(long long subsets);

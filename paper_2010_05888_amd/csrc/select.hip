@@ -1048,10 +1048,19 @@ hipError_t enqueue_peer_mda(const DistSums& ds, int nodes, const int32_t* peers,
 }
 
 namespace {
-// The enumeration spreads over the chip: 24 us with its second launch for 3,876
-// subsets and 17 to 22 for 5,005 and 6,188, where the covers take 23, 19 to 23
-// and 20 to 22; 30 against 24 for 33,649, 49 against 31 for 296,010.
+// The enumeration spreads over the chip and costs little where few rows are
+// kept; the covers cost more the more rows are left out. On N(0, 1) rows,
+// enumeration (with its second launch) against covers, for n rows and f left
+// out: 36.1 against 28.4 us for 24 and 4, 22.6 against 23.4 for 18 and 5, 26.4
+// against 23.4 for 19 and 5, 23.0 against 24.7 for 17 and 6, 24.5 against 25.0
+// for 19 and 6, 25.7 against 26.7 for 20 and 7, 19.3 against 27.4 for 17 and 8,
+// 25.1 against 28.5 for 20 and 9, 29.3 against 28.3 for 21 and 8, 31.6 against
+// 30.9 for 21 and 10, 50.9 against 28.6 for 23 and 8. With f outliers the covers
+// take 2 to 4 us less.
 constexpr int64_t kCoverFrom = int64_t{1} << 13;
+bool cover_pays(int n, int f, int64_t total) {
+  return total >= kCoverFrom && (n >= 21 || n >= 2 * f + 7);
+}
 int64_t g_mda_cover_min = kMdaCoverAutomatic;
 }  // namespace
 
@@ -1062,7 +1071,7 @@ void set_mda_cover_min(int64_t subsets) {
 
 bool mda_uses_cover(int n, int f) {
   const int64_t total = binomial(n, f), set = mda_cover_min();
-  return total < 0 || total >= (set == kMdaCoverAutomatic ? kCoverFrom : set);
+  return total < 0 || (set == kMdaCoverAutomatic ? cover_pays(n, f, total) : total >= set);
 }
 
 hipError_t enqueue_mda_select(const DistSums& ds, int f, void* scratch, int32_t* sel,

@@ -262,6 +262,13 @@ def test_every_threshold_of_the_cover_search_is_obeyed(lib):
         covers = bytes_at(0)
         assert bytes_at(automatic) == covers
         assert bytes_at(42_504) == covers
+        # few rows of which many are left out are enumerated (C(20, 8) = 125,970)
+        for n, f, by_covers in ((20, 8, False), (17, 6, False), (19, 6, True), (21, 8, True),
+                                (20, 5, True), (18, 5, True), (40, 4, True), (19, 9, False)):
+            gf.set_mda_cover_min(0)
+            least = gf.workspace_bytes("mda", n, f, 1000)
+            gf.set_mda_cover_min(automatic)
+            assert (gf.workspace_bytes("mda", n, f, 1000) == least) == by_covers, (n, f)
         for line in (42_505, 1 << 20, (1 << 20) + 1, 1 << 62):
             assert bytes_at(line) > covers, line
     finally:
