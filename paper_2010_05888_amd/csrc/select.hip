@@ -593,8 +593,15 @@ __global__ __launch_bounds__(kBlock) void k_mda_search(DistSums ds, int s, int64
   }
 }
 
-constexpr int64_t kPeerCoverMin = 256;
-static_assert(kPeerCoverMin <= kBlock, "a thread per subset");
+// A node's subsets are enumerated, one or two per thread, where that is faster
+// than the covers. One workgroup a node, N(0, 1) rows, enumeration against
+// covers for q peers and f left out: 11.6 us for C(10, 4) = 210; two per thread
+// 17.6 against 18.7 for 11 and 4, 19.3 against 21.5 for 12 and 4, 15.7 against
+// 19.0 for 11 and 5, 24.2 against 20.4 for 13 and 3 (a scan step costs with the
+// rows kept), 75 against 27 for 24 and 2; three 28.0 against 21.2 for 12 and 5.
+bool peer_enumerates(int q, int f, int64_t total) {
+  return total < kBlock || (total < 2 * kBlock && q - f <= 8);
+}
 
 // Contraction with MDA: workgroup v searches the C(q, f) subsets of its q
 // peers (positions in the peer list, distances gathered as k_peer_select
@@ -612,8 +619,11 @@ __global__ __launch_bounds__(kBlock) void k_peer_mda(DistSums ds, const int32_t*
   const ScanLds sl = carve_scan_lds(lds, q, s);
   double* D = sl.D;
   gather_peers(ds, peers + static_cast<int64_t>(v) * q, q, D, map);
-  // at most kPeerCoverMin - 1 subsets: one per thread, nothing to prune
-  const int64_t r0 = threadIdx.x, r1 = r0 < total ? r0 + 1 : r0;
+  // one or two subsets per thread (peer_enumerates): a shared bound would cost
+  // more than it prunes
+  const int64_t per = (total + kBlock - 1) / kBlock;
+  const int64_t r0 = static_cast<int64_t>(threadIdx.x) * per;
+  const int64_t r1 = r0 + per < total ? r0 + per : total;
   double best = __builtin_inf();
   int64_t best_r = INT64_MAX;
   mda_scan(D, q, s, r0, r1, sl.idx, sl.pm, nullptr, &best, &best_r);
@@ -1032,9 +1042,7 @@ hipError_t enqueue_peer_mda(const DistSums& ds, int nodes, const int32_t* peers,
                             int32_t* sel, hipStream_t s) {
   const int64_t total = binomial(q, f);
   if (total < 1) return hipErrorInvalidValue;
-  // One workgroup enumerates a node's subsets: 12 us for 120 of them, where the
-  // covers take 16, 31 against 21 for 455, 338 against 25 for 33,649.
-  if (total >= kPeerCoverMin) {
+  if (!peer_enumerates(q, f, total)) {
     launch("peer_cover", k_peer_cover, dim3(nodes), dim3(kCoverThreads), 0, s, ds, peers, q, f,
            sel);
     return hipGetLastError();

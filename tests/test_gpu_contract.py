@@ -198,6 +198,27 @@ def test_shared_rows(n, absent, extra):
         assert np.array_equal(got[v], (acc / q).astype(np.float32)), v
 
 
+@pytest.mark.parametrize("q,f,search", [(10, 4, "peer_mda"), (11, 4, "peer_mda"),
+                                        (11, 5, "peer_mda"), (12, 4, "peer_mda"),
+                                        (13, 3, "peer_cover"), (12, 5, "peer_cover"),
+                                        (23, 2, "peer_mda"), (24, 2, "peer_cover")])
+def test_mda_search_of_a_node(q, f, search):
+    """One or two subsets a thread, or covers: the search each size takes, and the
+    first subset of least diameter among small-integer ties from either."""
+    n = q + 1
+    rng = np.random.default_rng(100 * q + f)
+    x = rng.integers(-2, 3, size=(n, 33)).astype(np.float32)
+    peers = np.stack([rng.permutation(n)[:q] for _ in range(n)]).astype(np.int32)
+    xt, pt = torch.from_numpy(x).to(DEV), torch.from_numpy(peers).to(DEV)
+    gf.set_kernel_timing(True)
+    y = gf.contract_step("mda", xt, pt, f)
+    names = set(gf.kernel_timing())
+    gf.set_kernel_timing(False)
+    assert {"peer_mda", "peer_cover"} & names == {search}
+    want, _ = oracle.contract_step("mda", x, peers, f)
+    assert np.array_equal(y.cpu().numpy(), want)
+
+
 def test_shared_mean_leaves_out_what_is_not_finite():
     n, q, d = 12, 9, 1 << 18
     rng, x = _inputs(n, d, 3)
