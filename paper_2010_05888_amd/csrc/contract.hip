@@ -492,18 +492,42 @@ hipError_t bulyan_nodes_dispatch(int theta, int beta, const float* x, int n, int
 
 }  // namespace
 
+namespace {
+
+// Where the shared mean is the faster form. Its work per node grows with n, the
+// other's with k, so it takes most of the rows to be chosen; and it holds two
+// workgroups per CU from n = 20 on, in step with each other, so that short
+// inputs end in a round that leaves the chip half idle. How many times as fast
+// as the other form it is (the kernels alone, every node of n hearing all):
+//                 d = 330 K   400 K   700 K   1.5 M   2.5 M    4 M   11.2 M
+//   n =  9, k = 4    0.98     1.07    1.12    1.10    1.05    1.10    1.06
+//   n = 12, k = 6    1.07     1.03    1.22    1.09    1.00    1.12    1.07
+//   n = 16, k = 8    0.98     0.92    0.86    0.83    1.03    1.08    1.10
+//           k = 11   1.12     1.07    1.03    0.98    1.23    1.28    1.28
+//           k = 14   1.18     1.13    1.08    1.05    1.33    1.41    1.41
+//   n = 20, k = 10   0.71     0.77    0.86    0.80    0.98    1.06    1.11
+//           k = 13   0.77     0.81    0.90    0.87    1.07    1.19    1.22
+//           k = 17   0.85     0.91    1.04    1.01    1.22    1.35    1.42
+//   n = 28, k = 14   0.68     0.74    0.78    0.76    0.82    0.89    0.97
+//           k = 19   0.80     0.89    0.93    0.92    0.99    1.08    1.19
+//           k = 24   0.86     0.95    1.01    1.03    1.11    1.21    1.33
+//   n = 32, k = 8    0.50     0.56    0.58    0.57    0.58    0.64    0.76
+bool mean_shared_pays(int n, int k, int64_t d) {
+  if (n > kSharedMaxRows || d < kSharedMinCoords) return false;
+  if (d < int64_t{1} << 19) return n <= 18 && 6 * k >= 5 * n;
+  if (n <= 9) return true;
+  if (n <= 12) return 2 * k >= n;
+  if (d < int64_t{1} << 21) return 6 * k >= 5 * n;
+  if (d < int64_t{1} << 23) return 3 * k >= 2 * n;
+  return 2 * k > n;
+}
+
+}  // namespace
+
 hipError_t enqueue_mean_nodes(const float* x, int n, int64_t d, int nodes, const int32_t* rows,
                               int k, bool ascending, float* y, hipStream_t s) {
   if (d == 0 || nodes == 0) return hipSuccess;
-  // Against the form below, whose work per node grows with k where the shared
-  // form's grows with n: 1.1 to 1.3 times as fast with k near n (n = 9 to 32,
-  // d = 10^6 and 8 * 10^6), 0.83 with k = 1 of n = 32, 0.96 to 1.03 with k = 1 of
-  // n = 24. Short rows would leave its larger tiles too few workgroups (d = 10^5:
-  // 0.8 to 1.04). Below 2^20 coordinates few rows per node don't pay either: a
-  // Multi-Krum step with k = 3 of n = 14 at d = 3 * 10^5 takes 26.0 us in the form
-  // below and 28.9 us in this one, k = 14 of n = 20 at 2.7 * 10^5 42.9 and 41.4 us.
-  const bool rows_pay = d >= int64_t{1} << 20 ? 4 * k + 16 >= n : 3 * k >= 2 * n;
-  if (ascending && n <= kSharedMaxRows && rows_pay && d >= kSharedMinCoords)
+  if (ascending && mean_shared_pays(n, k, d))
     return mean_shared_dispatch<1>(x, n, d, nodes, rows, k, y, s);
   launch("mean_nodes", k_mean_nodes, dim3(tile_grid(d)), dim3(kBlock),
          static_cast<uint32_t>(tile_bytes(n, nodes * k)), s, x, n, d, nodes, rows, k, y);
