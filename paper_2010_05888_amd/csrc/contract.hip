@@ -534,13 +534,34 @@ hipError_t enqueue_mean_nodes(const float* x, int n, int64_t d, int nodes, const
   return hipGetLastError();
 }
 
+namespace {
+
+// Where the shared median is the faster form. It gains with every row a node
+// hears and loses with every one it does not, and its workgroups of 512
+// coordinates are too few for short inputs of few rows. How many times as fast
+// as the network over each node's values it is (the kernels alone):
+//                    d = 262 K   330 K   450 K   800 K   1.2 M   2.1 M   4 M   11.2 M
+//   n =  7, 1 absent    0.90     0.89    1.02    1.21    1.08    1.15   1.17    1.11
+//   n = 10, 3 absent    0.81     0.95    0.90    1.00    0.98    0.92   1.03    1.03
+//   n = 11, 3 absent    0.89     0.96    0.97    0.87    0.94    0.93   1.07    1.14
+//   n = 13, 4 absent    1.02     0.95    0.96    0.94    0.93    0.95   1.10    1.12
+//   n = 17, 4 absent    1.24     1.17    1.18    1.31    1.30    1.33   1.60    1.64
+//   n = 17, 5 absent    0.92     0.89    0.86    0.95    0.98    1.06   1.13    1.18
+//   n = 20, 6 absent    1.02     0.99    0.92    1.02    1.02    1.12   1.16    1.21
+//   n = 22, 6 absent    1.14     1.09    1.02    1.15    1.19    1.28   1.31    1.36
+bool median_shared_pays(int n, int k, int64_t d) {
+  const int absent = n - k;
+  if (n > kSharedMaxRows || absent > kSharedMaxAbsent || 3 * absent >= n) return false;
+  if (11 * absent >= 3 * n && n < 21) return d >= int64_t{1} << (n < 16 ? 22 : 21);
+  return d >= (n < 14 ? 3 * kSharedMinCoords / 2 : kSharedMinCoords);
+}
+
+}  // namespace
+
 hipError_t enqueue_median_nodes(const float* x, int n, int64_t d, int nodes, const int32_t* rows,
                                 int k, float* y, hipStream_t s) {
   if (d == 0 || nodes == 0) return hipSuccess;
-  // Against the network over each node's k values: 1.2 times as fast at n = 9
-  // with 2 absent, 2.2 at n = 24 with 5, 3.6 at n = 32 with 3; 0.9 to 0.97 at
-  // n = 16 with 6.
-  if (n <= kSharedMaxRows && n - k <= kSharedMaxAbsent && 3 * (n - k) < n && d >= kSharedMinCoords)
+  if (median_shared_pays(n, k, d))
     return median_shared_dispatch<1>(x, n, d, nodes, rows, k, y, s);
   return median_nodes_dispatch<1>(k, x, n, d, nodes, rows, y, s);
 }

@@ -167,35 +167,50 @@ def test_mda_small_integer_ties():
             assert np.array_equal(got[v], want[v]), (trial, n, q, f, v, want_sel[v])
 
 
-# the forms that share a coordinate's rows between the nodes, from 2^18
-# coordinates on: n at both sides of their limit of 32 rows, every count of
-# absent rows up to and past 6, whole and ragged tiles of 512 coordinates
+def _shared(n, absent):
+    """Coordinates from which on the median shares a coordinate's rows between
+    the nodes."""
+    if 11 * absent >= 3 * n and n < 21:
+        return 1 << (22 if n < 16 else 21)
+    return 3 << 17 if n < 14 else 1 << 18
+
+
+# the forms that share a coordinate's rows between the nodes, at the smallest
+# lengths that take them: n at both sides of their limit of 32 rows, every count
+# of absent rows up to and past 6, whole and ragged tiles of 512 coordinates
 @pytest.mark.parametrize("n,absent,extra", [(1, 0, 1), (3, 0, 0), (4, 1, 1), (8, 2, 511),
                                             (10, 3, 510), (13, 4, 2), (20, 5, 513), (19, 6, 2),
                                             (18, 6, 3), (32, 6, 1025), (32, 7, 188), (32, 0, 511),
                                             (33, 3, 188)])
 def test_shared_rows(n, absent, extra):
-    d = (1 << 18) + extra
+    d = _shared(n, absent) + extra
     q = n - absent
-    rng, x = _inputs(n, d, 7 * n + absent)
+    rng = np.random.default_rng(7 * n + absent)
+    g = torch.Generator(device=DEV).manual_seed(7 * n + absent)
+    xt = torch.randn((n, d), device=DEV, generator=g)
+    xt *= torch.from_numpy(1.0 + rng.permutation(n) / n).to(DEV).float()[:, None]
+    xt[: max(1, n // 8)] *= 10.0
     peers = np.stack([rng.permutation(n)[:q] for _ in range(n)]).astype(np.int32)
     if q > 1:
         peers[0, q - 1] = peers[0, 0]  # a list that repeats a row: the general form
-    xt, pt = torch.from_numpy(x).to(DEV), torch.from_numpy(peers).to(DEV)
-    got = gf.contract_step("median", xt, pt, 0).cpu().numpy()
-    srt = np.sort(x[peers].astype(np.float64), axis=1)
-    want = ((srt[:, (q - 1) // 2] + srt[:, q // 2]) / 2).astype(np.float32)
-    assert np.array_equal(got, want)
+    pt = torch.from_numpy(peers).to(DEV)
+    got = gf.contract_step("median", xt, pt, 0)
+    for v in range(n):
+        srt = xt[pt[v].long()].sort(0).values.double()
+        want = ((srt[(q - 1) // 2] + srt[q // 2]) / 2).float()
+        assert torch.equal(got[v], want), v
     if q < 3:
         return
     # Multi-Krum of all q rows: the selection is the list, in ascending order
     # (a list that repeats a row has no such selection)
-    got = gf.contract_step("multikrum", xt, pt, 0, q).cpu().numpy()
+    if n > 18:
+        xt = torch.cat([xt, xt.flip(1)], 1)  # where the mean shares too
+    got = gf.contract_step("multikrum", xt, pt, 0, q)
     for v in range(1, n):
-        acc = np.zeros(d)
+        acc = torch.zeros(xt.shape[1], dtype=torch.float64, device=DEV)
         for r in np.sort(peers[v]):
-            acc += x[r].astype(np.float64)
-        assert np.array_equal(got[v], (acc / q).astype(np.float32)), v
+            acc += xt[int(r)].double()
+        assert torch.equal(got[v], (acc / q).float()), v
 
 
 @pytest.mark.parametrize("q,f,search", [(10, 4, "peer_mda"), (11, 4, "peer_mda"),
@@ -220,7 +235,7 @@ def test_mda_search_of_a_node(q, f, search):
 
 
 def test_shared_mean_leaves_out_what_is_not_finite():
-    n, q, d = 12, 9, 1 << 18
+    n, q, d = 12, 9, 1 << 19
     rng, x = _inputs(n, d, 3)
     x[11, 700] = np.inf
     x[10, 40] = np.nan
@@ -233,11 +248,11 @@ def test_shared_mean_leaves_out_what_is_not_finite():
     assert np.array_equal(y, np.tile((acc / q).astype(np.float32), (n, 1)))
 
 
-@pytest.mark.parametrize("n,absent", [(5, 1), (9, 2), (12, 3), (20, 3), (20, 6)])
+@pytest.mark.parametrize("n,absent", [(5, 1), (9, 2), (12, 3), (20, 3), (20, 5)])
 def test_shared_median_leaves_out_what_is_nan(n, absent):
     """NaN and infinities in rows that a node does not hear leave its median as
     it is, for odd and even counts of rows and whole and ragged tiles."""
-    q, d = n - absent, (1 << 18) + 3
+    q, d = n - absent, _shared(n, absent) + 3
     rng, x = _inputs(n, d, 31 * n + absent)
     at = rng.random(d)
     x[n - 1, at < 0.5] = np.nan  # nobody hears the last rows
@@ -250,12 +265,12 @@ def test_shared_median_leaves_out_what_is_nan(n, absent):
     assert np.array_equal(got, np.tile(want, (n, 1)))
 
 
-@pytest.mark.parametrize("n,absent", [(4, 1), (9, 2), (12, 3), (20, 3), (19, 6), (8, 0)])
+@pytest.mark.parametrize("n,absent", [(4, 1), (9, 2), (12, 3), (20, 3), (22, 6), (8, 0)])
 def test_medians_keep_the_sign_of_a_zero(n, absent):
     """Rows with zeros of both signs, -0 before +0: the same bits from the form
     that shares a coordinate's rows and, on the first coordinates alone, from
     each node's own network."""
-    q, d = n - absent, (1 << 18) + 5
+    q, d = n - absent, _shared(n, absent) + 5
     rng = np.random.default_rng(n)
     x = rng.choice(np.array([-1.5, -0.0, 0.0, 0.0, 2.0], np.float32), (n, d))
     peers = np.stack([rng.permutation(n)[:q] for _ in range(n)]).astype(np.int32)
