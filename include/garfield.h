@@ -97,12 +97,13 @@ garfield_status garfield_pairwise_sqdist(const float* x, int n, int64_t d, doubl
  * every such sum is provably exact (the coordinate's exponents span at most
  * 23 binades), summing the selected vectors elsewhere: the same bits from
  * fewer bytes read.
- * Long inputs (3 <= n <= 20, m >= 2, d >= 2^23; also garfield_mda): the
- * selection is made beforehand on eight samples of 1,024 coordinates, and where
- * they agree the distance pass writes that selection's mean to out as well. Once
- * the selection itself is known, a last kernel finds it equal and ends, or writes
- * the mean as above (out may thus be written twice within the call). The output
- * does not depend on the samples.
+ * Long inputs (3 <= n <= 20, m >= 2, d >= 2^23, or 2^24 where n <= 10, m < n
+ * and 2m <= n + 4; also garfield_mda where n >= 2f+3): the selection is made
+ * beforehand on eight samples of 1,024 coordinates, and where they agree the
+ * distance pass writes that selection's mean to out as well. Once the selection
+ * itself is known, a last kernel finds it equal and ends, or writes the mean as
+ * above (out may thus be written twice within the call). The output does not
+ * depend on the samples.
  * Short inputs (n <= 12, out float-aligned, d up to about 10^5 coordinates)
  * take two launches instead of three or four: the distance pass, then one
  * kernel whose workgroups each add the distance partials, make the selection

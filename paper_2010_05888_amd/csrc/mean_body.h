@@ -106,10 +106,9 @@ __device__ __forceinline__ void mean_at(const Src& src, int64_t d, const L& rows
 // The mean of k distinct rows (sel, ascending; `chosen` their mask, n rows in
 // all) at the W coordinates c .. c+W-1 from the column sums: where all of them
 // are exact (not NaN) the rows not chosen are subtracted in ascending order,
-// two rows' loads in flight; otherwise, and without column sums (null), the
-// rows of sel are summed as mean_at sums them. Either way the fp64 value is
-// the exact sum mean_at forms (sums of these values are exact where the column
-// sum is), rounded once.
+// two rows' loads in flight; otherwise the rows of sel are summed as mean_at
+// sums them. Either way the fp64 value is the exact sum mean_at forms (sums of
+// these values are exact where the column sum is), rounded once.
 template <int W, class Src>
 __device__ __forceinline__ void complement_at(const Src& src, int n, int64_t d,
                                               const int32_t* __restrict__ sel, int k,
@@ -117,27 +116,25 @@ __device__ __forceinline__ void complement_at(const Src& src, int n, int64_t d,
                                               int64_t c, float* __restrict__ out) {
   const bool full = c + W <= d;
   double acc[W];
-  bool exact = colsum != nullptr;
-  if (exact) {
-    bool loaded = false;
-    if constexpr (W >= 2) {
-      if (full) {  // ordinary 16-byte loads: a line's halves meet in L2
+  bool loaded = false;
+  if constexpr (W >= 2) {
+    if (full) {  // ordinary 16-byte loads: a line's halves meet in L2
 #pragma unroll
-        for (int e = 0; e < W; e += 2) {
-          const d2 t = *reinterpret_cast<const d2*>(colsum + c + e);
-          acc[e] = t.x;
-          acc[e + 1] = t.y;
-        }
-        loaded = true;
+      for (int e = 0; e < W; e += 2) {
+        const d2 t = *reinterpret_cast<const d2*>(colsum + c + e);
+        acc[e] = t.x;
+        acc[e + 1] = t.y;
       }
+      loaded = true;
     }
-    if (!loaded) {
-#pragma unroll
-      for (int e = 0; e < W; ++e) acc[e] = (c + e < d) ? colsum[c + e] : 0.0;
-    }
-#pragma unroll
-    for (int e = 0; e < W; ++e) exact = exact && !__builtin_isnan(acc[e]);
   }
+  if (!loaded) {
+#pragma unroll
+    for (int e = 0; e < W; ++e) acc[e] = (c + e < d) ? colsum[c + e] : 0.0;
+  }
+  bool exact = true;
+#pragma unroll
+  for (int e = 0; e < W; ++e) exact = exact && !__builtin_isnan(acc[e]);
   if (exact) {
     uint64_t rest = ~chosen & (n == 64 ? ~uint64_t{0} : (uint64_t{1} << n) - 1);  // uniform
     while (rest) {

@@ -440,6 +440,8 @@ __global__ __launch_bounds__(kBlock) void k_guess(const float* __restrict__ x, i
 // mean of 7 rows: 132, 136 and 144 us).
 constexpr int kAfterChunks = 2;
 
+// SUMS: where no guess was agreed on, the column sums are there.
+template <bool SUMS>
 __global__ __launch_bounds__(kBlock) void k_mean_after(const float* __restrict__ x, int n,
                                                        int64_t d,
                                                        const int32_t* __restrict__ sel,
@@ -448,10 +450,12 @@ __global__ __launch_bounds__(kBlock) void k_mean_after(const float* __restrict__
   const bool guessed = guess_agrees(o.guess, &mask);
   const uint64_t chosen = rows_mask(sel, o.m, n);
   if (guessed && chosen == mask) return;
+  const MatrixRows src{x, d};
   int64_t c = (static_cast<int64_t>(blockIdx.x) * kAfterChunks * kBlock + threadIdx.x) * 4;
-  for (int k = 0; k < kAfterChunks && c < d; ++k, c += 4 * kBlock)
-    complement_at<4>(MatrixRows{x, d}, n, d, sel, o.m, chosen, guessed ? nullptr : o.colsum, c,
-                     o.out);
+  for (int k = 0; k < kAfterChunks && c < d; ++k, c += 4 * kBlock) {
+    if (SUMS && !guessed) complement_at<4>(src, n, d, sel, o.m, chosen, o.colsum, c, o.out);
+    else mean_at<4>(src, d, ListedRows{sel, n}, o.m, c, o.out);
+  }
 }
 
 template <int N>
@@ -519,14 +523,30 @@ bool ring_pays(int n, int64_t d) {
   return d >= int64_t{1} << (n >= 16 ? 21 : 23);
 }
 
-// A guess costs its launch and the look at it afterwards (4 to 10 us) and
-// saves a pass over m rows. Where the samples disagree nothing is saved: from
-// 8 M coordinates on the faster distance pass makes up for it (N(0, 1) rows,
-// Multi-Krum, n = 7 80.7 us with and without, n = 12 118 against 119; rows with
-// f outliers, where they agree: 56 against 83 us and 86 against 119).
+// A guess costs its launch and the look at it afterwards (4 to 10 us), and
+// where the samples agree it saves a pass over m rows. Where they disagree
+// nothing is saved, and the line is where the ring form's faster distance pass
+// still makes up for it. Multi-Krum with m = n - f, whole calls in us in the
+// register form without a guess, then in the ring form without one, with one
+// the samples disagree on (N(0, 1) rows) and with a right one (f outliers):
+//                          d = 8.4 M              d = 25.6 M
+//   n =  5, f = 1    63.2  61.8  66.4  48.1    171  167  171  122
+//   n =  7, f = 2    80.7  78.3  83.2  60.9    223  214  221  159
+//   n =  8, f = 1    92.3  85.4  89.9  68.9    254  235  238  180
+//   n = 11, f = 2     120   109   113  86.2    331  311  313  242
+//   n = 14, f = 2     172   157   169   122    504  452  467  327
+//   n = 17, f = 3     213   189   199   153    616  535  550  415
+//   n = 20, f = 4     251   220   234   194    735  645  667  539
+// Up to 10 rows the ring form gains too little below 2^24, except on calls with
+// column sums (2m > n + 4) and on those that keep every row, whose guess is
+// never wrong. A selection of fewer than n - f rows among rows alike is never
+// guessed right: n = 17, m = 8 157 us with a guess and 151 without, 176 in the
+// register form.
 bool guess_pays(int n, int64_t d, int f, int m, const float* out) {
-  return n >= 3 && n <= kGuessMaxN && n >= 2 * f + 3 && m >= 2 && out && load_width(out) == 4 &&
-         d >= int64_t{1} << 23 && d <= int64_t{1} << 38;
+  if (n < 3 || n > kGuessMaxN || n < 2 * f + 3 || m < 2 || !out || load_width(out) != 4)
+    return false;
+  const bool sure = n >= 11 || m == n || 2 * m > n + 4;
+  return d >= int64_t{1} << (sure ? 23 : 24) && d <= int64_t{1} << 38;
 }
 
 hipError_t enqueue_distances_ring(const float* x, const DistPlan& p, double* partial,
@@ -544,8 +564,9 @@ hipError_t enqueue_mean_after(const float* x, int n, int64_t d, const int32_t* s
   const int64_t per = int64_t{4} * kBlock * kAfterChunks;
   const int64_t groups = (d + per - 1) / per;
   if (groups > 0x7fffffff) return hipErrorInvalidValue;
-  launch("mean_after", k_mean_after, dim3(static_cast<unsigned>(groups)), dim3(kBlock), 0, s, x, n,
-         d, sel, RingOut{mean.guess, mean.colsum, mean.out, mean.m});
+  launch("mean_after", mean.colsum ? k_mean_after<true> : k_mean_after<false>,
+         dim3(static_cast<unsigned>(groups)), dim3(kBlock), 0, s, x, n, d, sel,
+         RingOut{mean.guess, mean.colsum, mean.out, mean.m});
   return hipGetLastError();
 }
 
