@@ -93,7 +93,11 @@ struct RingLoads {
       p[u] = src.row(k / PARTS) + c0 + (k % PARTS) * 256;
     }
   }
-  // Issue the next stage's loads into `slot`.
+  // Issue the next stage's loads into `slot`. No memory access written after
+  // them is moved ahead of them: ring_wait counts the stores that follow a
+  // stage's loads, and one that went first would leave it a store short, so that
+  // a stage could be read before it has landed. (Nothing else keeps the order: the
+  // rows are const and restrict, and the stores go elsewhere.)
   __device__ __forceinline__ void issue(float* slot, int64_t step, int wave, uint32_t lane) {
 #pragma unroll
     for (int u = 0; u < R::MAXPER; ++u) {
@@ -101,13 +105,14 @@ struct RingLoads {
         load_to_lds(p[u] + 4 * lane, slot + (wave + u * kRingWaves) * 256);
       p[u] += step;
     }
+    asm volatile("" ::: "memory");
   }
 };
 
 // Wait for this wave's loads of all but the last LEFT stages issued (`steady`),
 // else for all of them. STORES: vector stores this wave has issued, without
-// exception, since the loads waited for (stores and loads leave the count in
-// order).
+// exception, since the loads waited for (stores and loads leave the count in the
+// order they were issued in, which is that of the source, see issue).
 template <int N, int LEFT, int STORES = 0>
 __device__ __forceinline__ void ring_wait(bool steady, int wave) {
   using R = RingShape<N>;

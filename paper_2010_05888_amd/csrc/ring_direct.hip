@@ -220,9 +220,10 @@ __device__ __forceinline__ void ring_write(const RingOut& o, uint64_t mask, cons
   }
 }
 
-// Group GRP's share of the pass. The groups all hold every coordinate; the
-// waves of a group that write (WRITES) are its GRP-th part, so that each SIMD
-// has one writing wave of every two.
+// Group GRP's share of the pass. The groups all hold every coordinate, and the
+// part of a stage that a wave's lanes hold is written (WRITES) by the wave of one
+// group: with two groups waves 0, 1, 6 and 7, one on each SIMD; with four waves 0
+// and 5, on two of the four SIMDs.
 template <int N, int GRP, int WRITES>
 __device__ __forceinline__ void ring_pass(const float* __restrict__ x, int64_t d, float* lds,
                                           const RingOut& o, uint64_t mask, float* acc,
