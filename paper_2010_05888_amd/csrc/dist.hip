@@ -73,7 +73,6 @@ __global__ __launch_bounds__(kBlock) void k_dist_direct_sum(const float* __restr
 }
 
 // ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // Gram engine, step 1: probe. The sample is kProbeRuns runs of kBlock
 // consecutive coordinates spread evenly over d (all of d in one run when d is
 // smaller than the sample). Workgroup (i, r) sums (x_i - x_j)^2 for every j
@@ -1154,7 +1153,9 @@ hipError_t enqueue_distances(const float* x, const DistPlan& p, const DistWorksp
   hipError_t e = hipSuccess;
   if (colsum && (p.engine != kEngineDirect || p.n > kColSumMaxN)) return hipErrorInvalidValue;
   if (p.engine == kEngineNone) return hipSuccess;  // D is all zeros: nothing to compute
-  if (mean && (!p.ring || p.n > kGuessMaxN)) return hipErrorInvalidValue;
+  if (mean && (!p.ring || p.n < kGuessMinN || p.n > kGuessMaxN ||
+               (mean->colsum && p.n > kColSumMaxN)))
+    return hipErrorInvalidValue;
   if (p.ring) {
     if (colsum) return hipErrorInvalidValue;
     e = enqueue_distances_ring(x, p, ws.partial, mean, s);

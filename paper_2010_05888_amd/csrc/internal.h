@@ -74,7 +74,7 @@ hipError_t enqueue_reference(const float* x, const DistPlan& p, const DistWorksp
 // sum or a sum of some of the rows might not be exact (ColSum in
 // direct_body.h).
 constexpr int kColSumMaxN = 12;
-// mean (ring plans with n <= kGuessMaxN only): see RingMean.
+// mean (ring plans with kGuessMinN <= n <= kGuessMaxN only): see RingMean.
 struct RingMean;
 hipError_t enqueue_distances(const float* x, const DistPlan& p, const DistWorkspace& ws,
                              hipStream_t s, bool sum_tiles = true, double* colsum = nullptr,
@@ -98,7 +98,7 @@ hipError_t enqueue_distances_ring(const float* x, const DistPlan& p, double* par
 // null) as the plain step's colsum. enqueue_mean_after then finishes the call
 // once the selection itself is known: nothing is left to do when the guess was
 // right, else it writes the mean from the column sums or from the rows.
-constexpr int kGuessMaxN = 20;
+constexpr int kGuessMinN = 3, kGuessMaxN = 20;
 constexpr int kGuessRuns = 8;
 constexpr int kGuessRun = 1024;
 struct RingMean {

@@ -75,6 +75,16 @@ struct RingShape {
   static_assert((AHEAD - 1) * MAXPER < 64, "vmcnt has six bits");
 };
 
+// This lane's number, formed anew where it is used.
+__device__ __forceinline__ uint32_t fresh_lane() {
+  uint32_t lane;
+  asm volatile(
+      "v_mbcnt_lo_u32_b32 %0, -1, 0\n\t"
+      "v_mbcnt_hi_u32_b32 %0, -1, %0"
+      : "=v"(lane));
+  return lane;
+}
+
 // A wave's share of a stage's loads: one pointer per load (wave-uniform; the
 // lanes add 16 bytes each), all of which advance by the same `step` floats
 // from one stage of the workgroup to its next.

@@ -232,6 +232,10 @@ __device__ __forceinline__ void ring_pass(const float* __restrict__ x, int64_t d
   using S = RingDirect<N>;
   constexpr int M = S::L.count[GRP];
   constexpr bool ALL = WRITES != kNothing;
+  // 18 rows with the mean leave no register for the lane's number: the compiler
+  // kept it in memory, and reading it back there waited for every load in flight
+  // (533 us where this takes 463, 25.6 M coordinates and a right guess).
+  constexpr bool FRESH = N == 18 && WRITES == kMean;
   using Pairs = std::make_integer_sequence<int, M>;
   const uint32_t lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -252,7 +256,8 @@ __device__ __forceinline__ void ring_pass(const float* __restrict__ x, int64_t d
   if (cnt > 0) {
     RingLoads<N> loads;
     loads.start(src, b * R::STAGE, wave);
-    for (int u = 0; u < R::AHEAD && u < cnt; ++u) loads.issue(lds + u * R::SLOT, step, wave, lane);
+    for (int u = 0; u < R::AHEAD && u < cnt; ++u)
+      loads.issue(lds + u * R::SLOT, step, wave, FRESH ? fresh_lane() : lane);
     // Each pass's LDS reads are issued before the arithmetic of the pass
     // before it, the first of the next stage's among them: that stage has
     // landed by this one's barrier.
@@ -271,7 +276,8 @@ __device__ __forceinline__ void ring_pass(const float* __restrict__ x, int64_t d
       else
         ring_wait<N, R::AHEAD - 2>(i + R::AHEAD <= cnt, wave);
       lds_barrier();
-      if (i + R::AHEAD < cnt) loads.issue(lds + fill * R::SLOT, step, wave, lane);
+      if (i + R::AHEAD < cnt)
+        loads.issue(lds + fill * R::SLOT, step, wave, FRESH ? fresh_lane() : lane);
       fill = fill + 1 == R::SLOTS ? 0 : fill + 1;
       const float* after = lds + next * R::SLOT;
       next = next + 1 == R::SLOTS ? 0 : next + 1;
@@ -343,9 +349,14 @@ __device__ __forceinline__ void ring_direct(const float* __restrict__ x, int64_t
   for (int p = 0; p < M; ++p) sum[p] = 0.0;
   if constexpr (MEAN) {
     uint64_t mask;
-    if (guess_agrees(o.guess, &mask)) ring_pass<N, GRP, kMean>(x, d, lds, o, mask, acc, sum);
-    else if (o.colsum) ring_pass<N, GRP, kColsum>(x, d, lds, o, 0, acc, sum);
-    else ring_pass<N, GRP, kNothing>(x, d, lds, o, 0, acc, sum);
+    if (guess_agrees(o.guess, &mask)) {
+      ring_pass<N, GRP, kMean>(x, d, lds, o, mask, acc, sum);
+    } else if constexpr (N <= kColSumMaxN) {  // no call of more rows takes column sums
+      if (o.colsum) ring_pass<N, GRP, kColsum>(x, d, lds, o, 0, acc, sum);
+      else ring_pass<N, GRP, kNothing>(x, d, lds, o, 0, acc, sum);
+    } else {
+      ring_pass<N, GRP, kNothing>(x, d, lds, o, 0, acc, sum);
+    }
   } else {
     ring_pass<N, GRP, kNothing>(x, d, lds, o, 0, acc, sum);
   }
@@ -463,7 +474,7 @@ template <int N>
 hipError_t launch_ring(const float* x, const DistPlan& p, double* partial, const RingMean* mean,
                        hipStream_t s) {
   const RingOut o = mean ? RingOut{mean->guess, mean->colsum, mean->out, mean->m} : RingOut{};
-  if constexpr (N <= kGuessMaxN) {
+  if constexpr (N >= kGuessMinN && N <= kGuessMaxN) {
     if (mean) {
       launch("dist_ring_mean", k_dist_ring<N, true>, dim3(static_cast<unsigned>(p.tiles)),
              dim3(kRingThreads), 0, s, x, p.d, partial, o);
@@ -544,7 +555,7 @@ bool ring_pays(int n, int64_t d) {
 // guessed right: n = 17, m = 8 157 us with a guess and 151 without, 176 in the
 // register form.
 bool guess_pays(int n, int64_t d, int f, int m, const float* out) {
-  if (n < 3 || n > kGuessMaxN || n < 2 * f + 3 || m < 2 || !out || load_width(out) != 4)
+  if (n < kGuessMinN || n > kGuessMaxN || n < 2 * f + 3 || m < 2 || !out || load_width(out) != 4)
     return false;
   const bool sure = n >= 11 || m == n || 2 * m > n + 4;
   return d >= int64_t{1} << (sure ? 23 : 24) && d <= int64_t{1} << 38;
@@ -557,7 +568,7 @@ hipError_t enqueue_distances_ring(const float* x, const DistPlan& p, double* par
 
 hipError_t enqueue_guess(const float* x, int n, int64_t d, int f, int m, uint64_t* guess,
                          hipStream_t s) {
-  return guess_dispatch<3>(x, n, d, f, m, guess, s);
+  return guess_dispatch<kGuessMinN>(x, n, d, f, m, guess, s);
 }
 
 hipError_t enqueue_mean_after(const float* x, int n, int64_t d, const int32_t* sel,
