@@ -82,6 +82,19 @@ int garfield_tuning_table_gram_reference(const float* const* ptrs, int n, const 
                                          int K, void* stream);
 
 /*
+ * The selections a long input's mean is guessed from: Multi-Krum's selection of
+ * m rows (f as the rule's) on each of GARFIELD_TUNING_GUESS_RUNS samples of
+ * 1,024 consecutive coordinates, sample r from r * (d / GARFIELD_TUNING_GUESS_RUNS)
+ * on, as masks (bit i: row i) in masks[0 .. GARFIELD_TUNING_GUESS_RUNS-1] (HOST).
+ * Where they are all the same the distance pass writes that selection's mean.
+ * Enqueues them on `stream` and waits; needs 3 <= n <= 20, n >= 2f+3,
+ * 1 <= m <= n-f and d >= 8,192 (else GARFIELD_EINVAL). Returns a garfield_status.
+ */
+#define GARFIELD_TUNING_GUESS_RUNS 8
+int garfield_tuning_guess(const float* x, int n, int f, long long d, int m,
+                          unsigned long long* masks, void* stream);
+
+/*
  * Per-kernel timing. While on, every kernel a call launches is launched with
  * a pair of HIP events that the runtime stamps at the start and the end of
  * that kernel's own dispatch (hipExtLaunchKernelGGL), on the call's stream.

@@ -131,6 +131,8 @@ def load():
     lib.garfield_tuning_stream_read.restype = i32
     lib.garfield_tuning_table_gram_reference.argtypes = [vp, i32, vp, i32, vp]
     lib.garfield_tuning_table_gram_reference.restype = i32
+    lib.garfield_tuning_guess.argtypes = [vp, i32, i32, ctypes.c_longlong, i32, vp, vp]
+    lib.garfield_tuning_guess.restype = i32
     lib.garfield_tuning_set_kernel_timing.argtypes = [i32]
     lib.garfield_tuning_set_kernel_timing.restype = i32
     lib.garfield_tuning_kernel_timing.argtypes = [ctypes.c_char_p, ctypes.c_size_t]
@@ -569,6 +571,20 @@ def gram_reference(x: torch.Tensor) -> int:
     if ref < 0:
         raise GarfieldError(EHIP, "garfield_tuning_gram_reference", "probe failed")
     return ref
+
+
+GUESS_RUNS = 8  # GARFIELD_TUNING_GUESS_RUNS
+
+
+def guessed_selections(x: torch.Tensor, f: int, m: int | None = None) -> list:
+    """The selections of m rows that the mean of a long input is guessed from,
+    one per sample (synchronises the current stream)."""
+    x = _input(x)
+    n, d = x.shape
+    masks = (ctypes.c_ulonglong * GUESS_RUNS)()
+    _check(load().garfield_tuning_guess(_ptr(x), n, f, d, m or n - f, masks, _stream(x)),
+           "garfield_tuning_guess")
+    return [[i for i in range(n) if (mask >> i) & 1] for mask in masks]
 
 
 STREAM_READ_BLOCKS = 512  # GARFIELD_TUNING_READ_BLOCKS

@@ -247,6 +247,7 @@ garfield_status static_scratch(void** out) {
 
 static_assert(GARFIELD_NMAX == kNmax, "kernel limit and public limit differ");
 static_assert(GARFIELD_DIRECT_MAX_N_LIMIT == kDirectMaxNLimit, "direct engine limit differs");
+static_assert(GARFIELD_TUNING_GUESS_RUNS == kGuessRuns, "samples of a guess differ");
 static_assert(GARFIELD_MDA_COVER_AUTOMATIC == kMdaCoverAutomatic, "automatic line differs");
 
 }  // namespace
@@ -801,6 +802,22 @@ int garfield_tuning_table_gram_reference(const float* const* ptrs, int n, const 
     return -1;
   if (hipStreamSynchronize(s) != hipSuccess) return -1;
   return ref;
+}
+
+int garfield_tuning_guess(const float* x, int n, int f, long long d, int m,
+                          unsigned long long* masks, void* stream) {
+  if (check_common(x, n, f, d) != GARFIELD_OK || !masks || n < kGuessMinN || n > kGuessMaxN ||
+      n < 2 * f + 3 || m < 1 || m > n - f || d < kGuessRuns * kGuessRun)
+    return GARFIELD_EINVAL;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  void* base = nullptr;
+  const garfield_status st = workspace(kGuessRuns * sizeof(uint64_t), &base);
+  if (st != GARFIELD_OK) return st;
+  hipError_t e = enqueue_guess(x, n, d, f, m, static_cast<uint64_t*>(base), s);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(masks, base, kGuessRuns * sizeof(uint64_t), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  return to_status(e);
 }
 
 int garfield_tuning_set_kernel_timing(int on) {

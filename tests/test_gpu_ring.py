@@ -84,14 +84,31 @@ def _mean64(x, rows):
     return (acc / len(rows)).float()
 
 
+def _samples(x, f, m):
+    """Multi-Krum's selection on each of the guess's eight samples, and the least
+    gap between the scores of its last row in and its first row out."""
+    n, d = x.shape
+    picks, gap = [], 1.0
+    for r in range(8):
+        a = r * (d // 8)
+        D = _dist64(x[:, a:a + 1024]).tolist()
+        s = sorted((sum(sorted(D[i][j] for j in range(n) if j != i)[:n - f - 2]), i)
+                   for i in range(n))
+        picks.append(sorted(i for _, i in s[:m]))
+        if m < n:
+            gap = min(gap, s[m][0] / s[m - 1][0] - 1.0)
+    return picks, gap
+
+
 # m beside the default: with n <= 12 and 2m > n + 4 a disagreement leaves the
-# column sums, otherwise nothing
-@pytest.mark.parametrize("ends", ["right", "disagree", "wrong"])
-@pytest.mark.parametrize("rule,n,f,m,extra", [
-    ("multikrum", 3, 0, 3, 0), ("multikrum", 7, 1, 6, 1023), ("multikrum", 11, 2, 9, 511),
-    ("multikrum", 11, 2, 7, 1), ("multikrum", 12, 2, 10, 0), ("mda", 10, 3, 7, 1),
-    ("multikrum", 13, 2, 11, 511), ("mda", 16, 2, 14, 0), ("multikrum", 18, 4, 14, 1),
-    ("multikrum", 20, 4, 16, 511)])
+# column sums, otherwise nothing; a guess of every row is always right
+@pytest.mark.parametrize("rule,n,f,m,extra,ends", [
+    (*case, ends) for case in [
+        ("multikrum", 3, 0, 3, 0), ("multikrum", 7, 1, 6, 1023), ("multikrum", 11, 2, 9, 511),
+        ("multikrum", 11, 2, 7, 1), ("multikrum", 12, 2, 10, 0), ("mda", 10, 3, 7, 1),
+        ("multikrum", 13, 2, 11, 511), ("mda", 16, 2, 14, 0), ("multikrum", 18, 4, 14, 1),
+        ("multikrum", 20, 4, 16, 511)]
+    for ends in ["right", "disagree", "wrong"] if case[3] < case[1] or ends == "right"])
 def test_mean_on_a_guess(rule, n, f, m, extra, ends):
     d = (1 << (23 if n >= 11 or m == n or 2 * m > n + 4 else 24)) + extra
     x = _rows(n, d, 7 * n + m)
@@ -103,7 +120,7 @@ def test_mean_on_a_guess(rule, n, f, m, extra, ends):
         # values 2^30 apart in some coordinates: their column sums are not exact
         for r in range(n):
             x[r, 1001 * r::1001 * n] *= 2.0 ** 30
-    if ends == "wrong" and out_rows:
+    if ends == "wrong":
         # every sample (1,024 coordinates from r * (d // 8) on) shows others
         for r in range(8):
             a = r * (d // 8)
@@ -119,6 +136,16 @@ def test_mean_on_a_guess(rule, n, f, m, extra, ends):
     if ends != "disagree":
         assert want == [i for i in range(n) if i not in out_rows]
     assert torch.equal(out, _mean64(x, want))  # bit for bit: the same fp64 sum, rounded once
+    # the call did end that way: the kernel's fp32 sums of 1,024 squares (4 in a
+    # lane, then a tree) are within 16 * 2^-24, the scores' gap is wider than twice that
+    picks, gap = _samples(x, f, m)
+    assert gap > 2e-6
+    assert gf.guessed_selections(x, f, m) == picks
+    if ends == "disagree":
+        assert any(p != picks[0] for p in picks)
+    else:
+        assert all(p == picks[0] for p in picks)
+        assert (picks[0] == want) == (ends == "right")
 
 
 def test_column_sums_without_a_guess():
