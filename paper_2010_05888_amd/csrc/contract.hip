@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kBlock) void k_median_nodes(const float* __restrict
 // us for n = 20 nodes of 11.2 M coordinates and 17 peers.
 //
 // Both then run at 4.3 TB/s of rows read and rows written, the rate of a copy
-// on this chip (4.6).
+// on this chip (4.6); at 32 nodes the vector work per node bounds them again.
 //
 // A node whose list repeats a row (its mask has fewer rows) takes its listed
 // rows in order, and so do all nodes of a wave that holds what the shared work

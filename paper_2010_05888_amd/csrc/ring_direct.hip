@@ -10,8 +10,8 @@
 // hold accumulators only. Up to 12 rows the pass is bound by HBM: n = 11 at
 // 25.6 M coordinates 169 us, 6.65 TB/s (register form 190 us, 5.92), where a
 // plain read of one contiguous buffer reaches 6.9. From 16 rows on it is bound
-// by the vector unit, two instructions per pair and coordinate: n = 19 345 us,
-// its VALU busy 90 % of the time at the 1.95 GHz the chip holds under it
+// by the vector unit, two instructions per pair and coordinate: n = 19 349 us,
+// its VALU busy 90 % of the time at 2.0 GHz, and 330 to 500 as the clock goes
 // (register form 402 us). Tried and slower: every group reading all rows from
 // LDS (n = 17: 344 against 327 us), and one barrier per stage without the next
 // stage's LDS reads ahead of it (n = 14: 256 against 244 us).
