@@ -553,9 +553,9 @@ bool ring_pays(int n, int64_t d) {
 // column sums (2m > n + 4) and on those that keep every row, whose guess is
 // never wrong. (In a burst of 21 calls, under the clock's dip at its start, 15 to
 // 19 rows of 10 M coordinates take 3 % longer with a wrong guess than in the
-// register form, 11 rows 1 % less.) A selection of fewer than n - f rows among rows alike is never
-// guessed right: n = 17, m = 8 157 us with a guess and 151 without, 176 in the
-// register form.
+// register form, 7 rows 2 % longer, 11 rows 4 % less.) A selection of fewer than
+// n - f rows among rows alike is never guessed right: n = 17, m = 8 157 us with a
+// guess and 151 without, 176 in the register form.
 bool guess_pays(int n, int64_t d, int f, int m, const float* out) {
   if (n < kGuessMinN || n > kGuessMaxN || n < 2 * f + 3 || m < 2 || !out || load_width(out) != 4)
     return false;
